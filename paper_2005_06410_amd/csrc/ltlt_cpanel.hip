@@ -109,10 +109,8 @@ __global__ void __launch_bounds__(kPanelThreads, 1) cpanel_kernel(CPanelArgs ca)
   T* my_ai = my_ar + (TOT + 1);
   T* my_lr = my_ai + (TOT + 1);                    // my_lr[u + 1] = Re Lrow[u]
   T* my_li = my_lr + (TOT + 2);
-  __shared__ int s_p, s_posw, s_abort;
-  __shared__ double red_v[kPanelWaves];
-  __shared__ uint64_t red_k[kPanelWaves];
-  __shared__ T s_none;                             // NaN: no finite candidate at this step
+  __shared__ XRes s_x;                             // alpha NaN: no finite candidate at this step
+  __shared__ Cand red[kPanelWaves];
 
   const int row0 = j + 1 + w * R;
   const int rows_here = max(0, min(R, n - row0));
@@ -127,7 +125,6 @@ __global__ void __launch_bounds__(kPanelThreads, 1) cpanel_kernel(CPanelArgs ca)
   for (int k = 0; k < NG; ++k) { gre[k] = T(0); gim[k] = T(0); gni[k] = T(0); }
   if (lane == 0) { my_lr[0] = T(0); my_li[0] = T(0); }
   T cvr = T(0), cvi = T(0);
-  if (tid == 0) s_abort = 0;
   T lvr = T(0), lvi = T(0), lsg = T(1);
   if (my_row && part == 0) {
     lvr = Ar[(int64_t)pos + (int64_t)j * lda];
@@ -164,32 +161,22 @@ __global__ void __launch_bounds__(kPanelThreads, 1) cpanel_kernel(CPanelArgs ca)
     // ---- this wave's candidate: (|re| + |im|, position), first maximum; the
     //      candidate lane leaves its value in V for the agreement ----
     {
-      double av = -1.0;
-      if (active) {
-        const double m = (double)(fabs(cvr) + fabs(cvi));
-        if (m == m) av = m;
-      }
-      double bv;
-      int bi;
-      const int src = wave_first_max(av, active ? lp : INT32_MAX, bv, bi);
-      int wpos = 0;
-      if (src >= 0) {
-        wpos = __builtin_amdgcn_readlane(pos, src);
-        if (lane == src) {
+      const double m = (double)(fabs(cvr) + fabs(cvi));
+      const Cand c = make_cand(active && part == 0 && m == m, m, false, pos, lp);
+      if (first_max_lane<false>(c, true)) {
+        red[wave] = c;
+        if (cand_lp(c) != (unsigned)kIdxNone) {
           st_coh_t(&Vr[pos - (j + 1)], cvr);
           st_coh_t(&Vi[pos - (j + 1)], cvi);
         }
       }
-      if (lane == 0) {
-        red_v[wave] = src >= 0 ? bv : -1.0;
-        red_k[wave] = ((uint64_t)(uint32_t)bi << 32) | ((uint64_t)wpos << 1);
-      }
     }
-    exchange_pivot<T>(a, k + 1, k, wave, lane, w, red_v, red_k, s_p, s_posw, s_none, s_abort);
-    if (s_abort) return;
-    const int p = s_p;
-    const int posw = s_posw;
-    const bool none = s_none != s_none;
+    exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x);
+    const XRes xr = s_x;
+    const int p = xr.p;
+    const int posw = xr.posw;
+    const bool none = xr.alpha != xr.alpha;
+    if (p < 0) return;
 
     if (my_row && p != k + 1) {
       if (lp == p) lp = k + 1;

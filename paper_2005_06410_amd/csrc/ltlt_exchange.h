@@ -14,20 +14,28 @@ constexpr int KC = 64;                                   // multiplier slots per
 // Lanes per row and register slots per lane for a block of width bw.
 inline int panel_split(int bw) { return bw <= KC ? 1 : (bw <= 2 * KC ? 2 : 4); }
 
+// A pivot candidate on its way from lanes to waves to workgroups:
+//   v = bits(|cv|) (a non-negative double)
+//   w = (sign(cv) << 42) | (pos << 21) | lp;  lp = kIdxNone: no candidate, v = 0
 // Record words.  s is the step stamp (1 <= s < 2^21; it grows by one per
 // exchange, so consecutive exchanges use alternate record slots).
-//   word A = bits(|cv|) | epoch(s) << 63,   epoch(s) = (s >> 1) & 1
-//   word B = (s << 43) | (sign(cv) << 42) | (pos << 21) | lp
+//   word A = v | epoch(s) << 63,   epoch(s) = (s >> 1) & 1
+//   word B = (s << 43) | w
 // A record slot alternates with s & 1 and every record location is written at
 // every step of its slot, so a slot holds stamp s or s-2 and the epoch bit
 // alone tells them apart in word A; word B carries the full stamp.
 constexpr uint64_t kIdxNone = 0x1FFFFFull;
-__device__ __forceinline__ uint64_t rec_a(double absv, int s) {
-  return ((uint64_t)__double_as_longlong(absv) & 0x7FFFFFFFFFFFFFFFull) | ((uint64_t)((s >> 1) & 1) << 63);
+struct __align__(16) Cand {
+  uint64_t v, w;
+};
+__device__ __forceinline__ Cand make_cand(bool on, double absv, bool neg, int pos, int lp) {
+  Cand c;
+  c.v = on ? (uint64_t)__double_as_longlong(absv) : 0ull;
+  c.w = on ? ((uint64_t)(((unsigned)neg << 10) | ((unsigned)pos >> 11)) << 32) | (((unsigned)pos << 21) | (unsigned)lp) : kIdxNone;
+  return c;
 }
-__device__ __forceinline__ uint64_t rec_b(int s, int sgn, int pos, uint64_t idx) {
-  return ((uint64_t)s << 43) | ((uint64_t)sgn << 42) | ((uint64_t)pos << 21) | idx;
-}
+__device__ __forceinline__ unsigned cand_lp(const Cand& c) { return (unsigned)c.w & (unsigned)kIdxNone; }
+__device__ __forceinline__ uint64_t rec_epoch(int s) { return (uint64_t)((s >> 1) & 1) << 63; }
 __device__ __forceinline__ bool rec_valid(uint64_t a, uint64_t b, int s) {
   return (int)(a >> 63) == ((s >> 1) & 1) && (int)(b >> 43) == s;
 }
@@ -120,54 +128,99 @@ __device__ __forceinline__ T part_sum(T v) {
   return v;
 }
 
+// Maximum of an unsigned key over lanes 0-7 (DPP row shifts 1, 2, 4; the
+// result sits in lane 7).
+__device__ __forceinline__ unsigned oct_umax(unsigned x) {
+  asm volatile(
+      "s_nop 1\n"
+      "v_max_u32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n"
+      "s_nop 1\n"
+      "v_max_u32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n"
+      "s_nop 1\n"
+      "v_max_u32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n"
+      "s_nop 1\n"
+      : "+v"(x));
+  return (unsigned)__builtin_amdgcn_readlane((int)x, 7);
+}
+
+// True in the lane (among those with `in`) that holds the first maximum: the
+// largest v, and among equal ones the smallest lp.  When no lane has a
+// candidate it is true in every `in` lane (they hold the same "none").  The
+// maximum is taken over the high words of v (order-preserving, +1 so that 0
+// means none); lanes that tie there are resolved by two more reductions, over
+// the low words and then the positions.  The winner is left as a lane mask, not
+// read out to scalars: the lane itself stores its candidate where it is
+// needed, which keeps the chain of lane reads (each waits for the vector unit)
+// off the step.  The step is bound by such chains, not by memory alone: clock
+// stamps gave about 900 cycles to a wave's own maximum, 700 to the merge of
+// the eight waves one after the other and 700 to the reduction of the records;
+// with lane-resident winners and the eight waves merged across lanes a column
+// step takes 3.26 -> 2.60 us with one workgroup and the n = 16384
+// factorization 107.4 -> 97.4 ms (complex n = 1501: 8.44 -> 7.41 ms), factors
+// bit-identical.
+template <bool OCT>
+__device__ __forceinline__ bool first_max_lane(const Cand& c, bool in) {
+  const bool some = in && cand_lp(c) != (unsigned)kIdxNone;
+  const unsigned hk = some ? (unsigned)(c.v >> 32) + 1u : 0u;
+  const unsigned mh = OCT ? oct_umax(hk) : wave_umax(hk);
+  bool tie = in && hk == mh;
+  const unsigned long long b = __ballot(tie);
+  if (__builtin_expect((b & (b - 1)) != 0 && mh != 0, 0)) {
+    const unsigned lo = (unsigned)c.v;
+    const unsigned ml = OCT ? oct_umax(tie ? lo : 0u) : wave_umax(tie ? lo : 0u);
+    tie = tie && lo == ml;
+    const unsigned nk = tie ? ~cand_lp(c) : 0u;
+    const unsigned mk = OCT ? oct_umax(nk) : wave_umax(nk);
+    tie = tie && nk == mk;
+  }
+  return tie;
+}
+
+// This wave's candidate: the first maximum of its lanes' goes into red[wave].
+__device__ __forceinline__ void wave_candidate(Cand* red, int wave, const Cand& c) {
+  if (first_max_lane<false>(c, true)) red[wave] = c;
+}
+
 // One grid-wide pivot agreement, in two halves called by every thread of the
 // workgroup (work that does not depend on the pivot may run in between).
-// Each wave has put its first-maximum candidate in red_v / red_k (lane 0:
-// |cv|, key = position << 32 | block-start index << 1 | sign).
+// Each wave has put its candidate in red (wave_candidate).
 // exchange_publish: every wave waits for its own earlier stores (so a
 // validated record implies they are visible), a barrier, then wave 0 merges
-// the waves and publishes the workgroup's record for stamp s.
+// the waves (lane i takes wave i's candidate) and the winning lane stores the
+// workgroup's record for stamp s.
 // exchange_collect: wave 0 polls every record until all carry stamp s and
 // reduces them (largest magnitude, then smallest position); the result lands
-// in s_p (pivot position), s_posw (its block-start index) and s_alpha
-// (signed pivot value; NaN and p = k+1 when no finite candidate exists),
-// handed to the other waves by a barrier.  A wait that exceeds its bound, or
-// finds the call's abort flag raised, raises the status words and s_abort.
+// in res: p (pivot position), posw (its block-start index) and alpha (signed
+// pivot value; NaN and p = posw = k+1 when no finite candidate exists), handed
+// to the other waves by a barrier.  A wait that exceeds its bound, or finds the
+// call's abort flag raised, raises the status words and leaves p = -1.
+struct __align__(16) XRes {
+  double alpha;
+  int p, posw;
+};
+
 __device__ __forceinline__ void exchange_publish(const PanelArgs& a, int s, int wave, int lane, int w,
-                                                 const double* red_v, const uint64_t* red_k) {
+                                                 const Cand* red) {
   uint64_t* recs = a.rec + (size_t)(s & 1) * (size_t)a.nrec * kRecStride;
   wait_stores();
   __syncthreads();
   if (wave == 0) {
-    double cb = red_v[0];
-    uint64_t ck = red_k[0];
-#pragma unroll
-    for (int wv = 1; wv < kPanelWaves; ++wv) {
-      const double ov = red_v[wv];
-      const uint64_t ok = red_k[wv];
-      const bool take = (ov > cb) | ((ov == cb) & (ok < ck));
-      cb = take ? ov : cb;
-      ck = take ? ok : ck;
-    }
-    if (lane == 0) {
-      const int ci = (int)(ck >> 32);
-      const bool none = ci == INT32_MAX;
-      st_coh64(&recs[(size_t)kRecStride * w + 0], rec_a(none ? 0.0 : cb, s));
-      st_coh64(&recs[(size_t)kRecStride * w + 1],
-               rec_b(s, (int)(ck & 1), (int)((ck >> 1) & kIdxNone), none ? kIdxNone : (uint64_t)ci));
+    const Cand c = red[lane & (kPanelWaves - 1)];
+    if (first_max_lane<true>(c, lane < kPanelWaves)) {
+      st_coh64(&recs[(size_t)kRecStride * w + 0], c.v | rec_epoch(s));
+      st_coh64(&recs[(size_t)kRecStride * w + 1], c.w | ((uint64_t)s << 43));
     }
   }
 }
 
-template <typename T>
-__device__ __forceinline__ void exchange_collect(const PanelArgs& a, int s, int k, int wave, int lane, int& s_p,
-                                                 int& s_posw, T& s_alpha, int& s_abort) {
+__device__ __forceinline__ void exchange_collect(const PanelArgs& a, int s, int k, int wave, int lane, XRes& res) {
   const int P = a.P;
   const uint64_t* recs = a.rec + (size_t)(s & 1) * (size_t)a.nrec * kRecStride;
   if (wave == 0) {
     const int q_n = (P + kWave - 1) / kWave;
     const uint64_t t0 = wall_ticks();
     uint64_t ra[kPollPerLane], rb[kPollPerLane];
+    bool gave_up = false;
     for (;;) {
 #pragma unroll
       for (int q = 0; q < kPollPerLane; ++q) {
@@ -186,51 +239,46 @@ __device__ __forceinline__ void exchange_collect(const PanelArgs& a, int s, int 
       }
       // a wait of this call that gave up elsewhere ends this one too, even
       // when every record has arrived
-      if (stv != 0 || (__ballot(!ok) != 0 && wall_ticks() - t0 > kWaitLimitTicks)) {
-        if (lane == 0) { raise_wait_status(a.status); s_abort = 1; }
+      const bool all = __ballot(!ok) == 0;
+      if (stv != 0 || (!all && wall_ticks() - t0 > kWaitLimitTicks)) {
+        if (lane == 0) raise_wait_status(a.status);
+        gave_up = true;
         break;
       }
-      if (__ballot(!ok) == 0) break;
+      if (all) break;
       __builtin_amdgcn_s_sleep(0);
     }
-    double gv = -1.0;
-    int gi = INT32_MAX, gpos = 0, gsg = 0;
+    // this lane's best of its records (lane, lane + 64, ...): positions rise
+    // with neither, so ties compare them
+    Cand c{0ull, kIdxNone};
 #pragma unroll
     for (int q = 0; q < kPollPerLane; ++q) {
       const int u = q * kWave + lane;
       if (q < q_n && u < P) {
-        const double av = __longlong_as_double((long long)(ra[q] & 0x7FFFFFFFFFFFFFFFull));
-        const int ix = (int)(rb[q] & kIdxNone);
-        const bool take = ((uint64_t)ix != kIdxNone) & ((av > gv) | ((av == gv) & (ix < gi)));
-        gv = take ? av : gv;
-        gi = take ? ix : gi;
-        gpos = take ? (int)((rb[q] >> 21) & kIdxNone) : gpos;
-        gsg = take ? (int)((rb[q] >> 42) & 1) : gsg;
+        const Cand o{ra[q] & 0x7FFFFFFFFFFFFFFFull, rb[q] & 0x7FFFFFFFFFFull};
+        const bool take = q == 0 || o.v > c.v || (o.v == c.v && cand_lp(o) < cand_lp(c));
+        c.v = take ? o.v : c.v;
+        c.w = take ? o.w : c.w;
       }
     }
-    double vmax;
-    int kmin;
-    const int src = wave_first_max(gv, gi, vmax, kmin);
-    if (lane == 0) {
-      if (src < 0) {                              // no finite candidate: no exchange
-        s_p = k + 1; s_posw = k + 1; s_alpha = T(NAN);
-      } else {
-        s_p = kmin;
-        s_posw = __builtin_amdgcn_readlane(gpos, src);
-        s_alpha = __builtin_amdgcn_readlane(gsg, src) ? -(T)vmax : (T)vmax;
-      }
+    if (first_max_lane<false>(c, true)) {
+      const bool none = cand_lp(c) == (unsigned)kIdxNone;   // no finite candidate: no exchange
+      const double v = __longlong_as_double((long long)c.v);
+      XRes r;
+      r.alpha = none ? (double)NAN : ((c.w >> 42) & 1 ? -v : v);
+      r.p = gave_up ? -1 : (none ? k + 1 : (int)cand_lp(c));
+      r.posw = none ? k + 1 : (int)((c.w >> 21) & kIdxNone);
+      res = r;
     }
   }
   __syncthreads();
 }
 
 // Both halves back to back.
-template <typename T>
 __device__ __forceinline__ void exchange_pivot(const PanelArgs& a, int s, int k, int wave, int lane, int w,
-                                               const double* red_v, const uint64_t* red_k, int& s_p,
-                                               int& s_posw, T& s_alpha, int& s_abort) {
-  exchange_publish(a, s, wave, lane, w, red_v, red_k);
-  exchange_collect<T>(a, s, k, wave, lane, s_p, s_posw, s_alpha, s_abort);
+                                               const Cand* red, XRes& res) {
+  exchange_publish(a, s, wave, lane, w, red);
+  exchange_collect(a, s, k, wave, lane, res);
 }
 
 }  // namespace ltlt

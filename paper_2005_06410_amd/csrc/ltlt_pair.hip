@@ -129,10 +129,8 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
   T* bufB = reinterpret_cast<T*>(wl);              // slots of the pivot row
   T* bufQ = bufB + TOT;                            // slots of row q
   T* gcol = bufQ + TOT;                            // g of the current column, by slot
-  __shared__ int s_p, s_posw, s_abort;
-  __shared__ double red_v[kPanelWaves];
-  __shared__ uint64_t red_k[kPanelWaves];
-  __shared__ T s_alpha;
+  __shared__ XRes s_x;
+  __shared__ Cand red[kPanelWaves];
 
   const int row0 = j + 1 + w * R;
   const int rows_here = max(0, min(R, n - row0));
@@ -144,7 +142,6 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
 #pragma unroll
   for (int c = 0; c < KC; ++c) L[c] = T(0);
   for (int s = lane; s < TOT; s += kWave) gcol[s] = T(0);
-  if (tid == 0) s_abort = 0;
   // Positions that received a displaced row, in registers: entry e (lane e,
   // or lane e-64 of the second pair) = (position, block-start index).  The
   // last entry with position x names the row at x; a position never listed
@@ -178,26 +175,11 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
 
     // ---- pivot candidate of column k ----
     {
-      double av = -1.0;
-      if (active) {
-        const double m = (double)fabs(cv);
-        if (m == m) av = m;
-      }
-      double bv;
-      int bi;
-      const int src = wave_first_max(av, active ? lp : INT32_MAX, bv, bi);
-      int wpos = 0, wsg = 0;
-      if (src >= 0) {
-        wpos = __builtin_amdgcn_readlane(pos, src);
-        wsg = __builtin_amdgcn_readlane(cv < T(0) ? 1 : 0, src);
-      }
-      if (lane == 0) {
-        red_v[wave] = src >= 0 ? bv : -1.0;
-        red_k[wave] = ((uint64_t)(uint32_t)bi << 32) | ((uint64_t)wpos << 1) | (uint64_t)wsg;
-      }
+      const double m = (double)fabs(cv);
+      wave_candidate(red, wave, make_cand(active && part == 0 && m == m, m, cv < T(0), pos, lp));
     }
     const int stamp = k / 2 + 1;
-    exchange_publish(a, stamp, wave, lane, w, red_v, red_k);
+    exchange_publish(a, stamp, wave, lane, w, red);
 
     // ---- column k+2 for the row qq at position k+2 (independent of the
     //      pivot unless it comes from k+2): its slots, S(pos, qq), cA = column
@@ -246,11 +228,12 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
     const int displaced = lookup(k + 1);           // row at position k+1 before the exchange
     if (!last && rowwave) spec(qs);
 
-    exchange_collect<T>(a, stamp, k, wave, lane, s_p, s_posw, s_alpha, s_abort);
-    if (s_abort) return;
-    const int p = s_p;
-    const int posw = s_posw;
-    const T alph = s_alpha;
+    exchange_collect(a, stamp, k, wave, lane, s_x);
+    const XRes xr = s_x;
+    const int p = xr.p;
+    const int posw = xr.posw;
+    const T alph = (T)xr.alpha;
+    if (p < 0) return;
     // the row at position k+2 after the exchange: the displaced row when the
     // pivot came from k+2, else the same as before
     const int q = last ? 0 : (p == k + 2 ? displaced : qs);

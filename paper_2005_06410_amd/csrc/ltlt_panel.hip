@@ -40,8 +40,8 @@
 // g from LDS.
 //
 // Exchange per step (one grid-wide round, no counters, no fences): every
-// workgroup merges the candidates of its waves and publishes the result as
-// one record of two self-validating 64-bit words (each carries the step
+// workgroup merges the candidates of its waves (one lane per wave) and the
+// winning lane publishes the result as one record of two self-validating 64-bit words (each carries the step
 // stamp); records sit 256 bytes apart.  Wave 0 of every workgroup polls all
 // records until each carries the current stamp and reduces them (largest
 // magnitude, then smallest position: the first maximum in position order), so
@@ -96,12 +96,8 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
 
   T* my_alpha = reinterpret_cast<T*>(smem) + wave * panel_wave_lds_elems(TOT);   // alpha_{j+u}
   T* my_lrowp = my_alpha + (TOT + 1);              // my_lrowp[u + 1] = Lrow[u]
-  // the agreement's results, read back together in one LDS round trip
-  struct __align__(16) XRes { int p, posw, abort, pad; };
-  __shared__ XRes s_x;
-  __shared__ double red_v[kPanelWaves];
-  __shared__ uint64_t red_k[kPanelWaves];
-  __shared__ T s_alpha;
+  __shared__ XRes s_x;                             // the agreement's result
+  __shared__ Cand red[kPanelWaves];
 
   const int row0 = j + 1 + w * R;                 // first block-start index held
   const int rows_here = max(0, min(R, n - row0));
@@ -116,7 +112,6 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   for (int k = 0; k < NG; ++k) gr[k] = T(0);
   if (lane == 0) my_lrowp[0] = T(0);               // Lrow[-1]: only ever multiplied, kept finite
   T cv = T(0);
-  if (tid == 0) s_x.abort = 0;
   // stored column value of this row and its sign (S(a,b) = -A(b,a) above the
   // diagonal); the sign is applied in the refresh so that no code waits for
   // the load before then.  First column: index j, rows >= j+1 (lower part).
@@ -141,33 +136,18 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
     }
     if (t == bw) break;                           // carry column formed
 
-    // ---- this wave's pivot candidate: (|cv|, position), first maximum ----
+    // ---- this wave's pivot candidate: (|cv|, position), first maximum; one
+    //      lane per row, NaN is never a candidate ----
     {
-      double av = -1.0;
-      if (active) {
-        const double m = (double)fabs(cv);
-        if (m == m) av = m;                        // NaN is never a candidate
-      }
-      double bv;
-      int bi;
-      const int src = wave_first_max(av, active ? lp : INT32_MAX, bv, bi);
-      int wpos = 0, wsg = 0;
-      if (src >= 0) {
-        wpos = __builtin_amdgcn_readlane(pos, src);
-        wsg = __builtin_amdgcn_readlane(cv < T(0) ? 1 : 0, src);
-      }
-      if (lane == 0) {
-        red_v[wave] = src >= 0 ? bv : -1.0;
-        red_k[wave] = ((uint64_t)(uint32_t)bi << 32) | ((uint64_t)wpos << 1) | (uint64_t)wsg;
-      }
+      const double m = (double)fabs(cv);
+      wave_candidate(red, wave, make_cand(active && part == 0 && m == m, m, cv < T(0), pos, lp));
     }
-    exchange_pivot<T>(a, k + 1, k, wave, lane, w, red_v, red_k, s_x.p, s_x.posw, s_alpha, s_x.abort);
-    const int4 xr = *reinterpret_cast<const int4*>(&s_x);
-    const T alph = s_alpha;
-    asm volatile("" ::"v"(xr.x), "v"(xr.y), "v"(xr.z), "v"(alph));   // both reads issued before the branch
-    if (xr.z) return;
-    const int p = xr.x;
-    const int posw = xr.y;                         // block-start index of the pivot row
+    exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x);
+    const XRes xr = s_x;
+    const T alph = (T)xr.alpha;
+    const int p = xr.p;
+    const int posw = xr.posw;                      // block-start index of the pivot row
+    if (p < 0) return;
 
     // ---- exchange positions k+1 and p (logical only) ----
     if (my_row && p != k + 1) {
