@@ -262,10 +262,14 @@ int factor_impl(int64_t n64, T* A, int64_t lda, int32_t* ipiv, int nb, hipStream
   Carve cv;
   const size_t o_PO = cv.take<T>((size_t)ldw * (nb + 1));
   const size_t o_Bm = cv.take<T>((size_t)ldw * (nb + 1));
-  const size_t o_G = cv.take<T>((size_t)ldw * nb);
+  const size_t o_G = cv.take<T>((size_t)ldw * panel_g_cols(bw0));   // no block is wider than the first
   const size_t o_al = cv.take<T>((size_t)nb);
   const size_t o_T = cv.take<int>((size_t)std::max(nblk, 1) * n);
-  const size_t o_GC = cv.take<int>((size_t)std::max(nblk, 1) * n);
+  // the panels' tail and the final row order (formed after the last panel)
+  // share their place
+  const size_t tail_elems = panel_tail_elems(bw0, ldw);
+  const size_t gc_bytes = std::max((size_t)std::max(nblk, 1) * n * sizeof(int), tail_elems * sizeof(T));
+  const size_t o_GC = cv.take<char>(gc_bytes);
   const int nrec = Pmax;                      // exchange records per slot
   const size_t o_rec = cv.take<uint64_t>((size_t)2 * kRecStride * nrec);
   const size_t o_st = cv.take<T>(perm_stage_elems<T>(n, c_end));
@@ -308,7 +312,7 @@ int factor_impl(int64_t n64, T* A, int64_t lda, int32_t* ipiv, int nb, hipStream
     pa.R = choose_rows<T>(bw);
     pa.P = (m + pa.R - 1) / pa.R;
     pa.nrec = nrec;
-    pa.G = Gm; pa.PO = PO; pa.Bm = Bm; pa.ldw = ldw; pa.alpha = al;
+    pa.G = Gm; pa.tail = Gc; pa.PO = PO; pa.Bm = Bm; pa.ldw = ldw; pa.alpha = al;
     pa.perm = Tblk + (int64_t)J * n;
     pa.ipiv = ipiv;
     pa.rec = rec;

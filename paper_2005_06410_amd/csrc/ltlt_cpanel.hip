@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(kPanelThreads, 1) cpanel_kernel(CPanelArgs ca)
         }
       }
     }
-    exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x);
+    exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x, [](int) {});
     const XRes xr = s_x;
     const int p = xr.p;
     const int posw = xr.posw;

@@ -59,36 +59,136 @@ __device__ __forceinline__ T ld_coh_t(const T* p) {
 // accesses across this point.
 __device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// L[c] = v where `on`, for a wave-uniform slot c: a uniform branch on the
-// group of 16 slots, then selects inside the group, so that register indices
-// stay static and the other 48 slots are untouched.
-#define LTLT_SET_GROUP(G0)                                                       \
-  if ((c >> 4) == (G0) / 16) {                                                  \
-    _Pragma("unroll") for (int i = 0; i < 16; ++i) L[(G0) + i] = (on && c == (G0) + i) ? v : L[(G0) + i]; \
-  }
-
-// L[c] = v where `on`, for a wave-uniform slot c < KC: a uniform jump to the
-// one slot (register indices stay static and only that slot is written),
-// instead of LTLT_SET_GROUP's selects over a whole group of 16.  Measured
-// faster in the two- and four-lane-per-row panels; with one lane per row the
-// jump table's control flow pushed the kernel past its register budget, so
-// that panel keeps the group form.
-#define LTLT_SLOT_CASE(i) \
-  case (i): L[(i)] = on ? v : L[(i)]; break;
-#define LTLT_SLOT_CASE4(i) LTLT_SLOT_CASE(i) LTLT_SLOT_CASE((i) + 1) LTLT_SLOT_CASE((i) + 2) LTLT_SLOT_CASE((i) + 3)
-#define LTLT_SLOT_CASE16(i) \
-  LTLT_SLOT_CASE4(i) LTLT_SLOT_CASE4((i) + 4) LTLT_SLOT_CASE4((i) + 8) LTLT_SLOT_CASE4((i) + 12)
-template <typename T>
-__device__ __forceinline__ void set_slot(T (&L)[KC], int c, bool on, T v) {
+// acc[c % 4] += g[c % 4](lane (lane & ~15) + c / 4) * L[c] for the slots c <
+// nslots (wave-uniform, 0 <= nslots <= 64; up to the next multiple of 8, where
+// the slots hold zeros), oldest first, through v_fmac with a DPP row broadcast
+// (row_newbcast, gfx950).  One asm block with its own exits: groups of 16 behind
+// branches that the compiler lays out cost a jump out and back each.  It is led
+// by the two wait states a DPP read needs after a vector write of its source.
+#define LTLT_SLOT_FMA(OP, c, k, b) \
+  OP " %[a" #k "], %[g" #k "], %[l" #c "] row_newbcast:" #b " row_mask:0xf bank_mask:0xf\n"
+#define LTLT_SLOT_END(c) "s_cmp_le_i32 %[ns], " #c "\ns_cbranch_scc1 LTLT_fma%=\n"
+#define LTLT_SLOT_FMAS(OP) \
+  LTLT_SLOT_FMA(OP, 0, 0, 0) LTLT_SLOT_FMA(OP, 1, 1, 0) LTLT_SLOT_FMA(OP, 2, 2, 0) LTLT_SLOT_FMA(OP, 3, 3, 0) \
+  LTLT_SLOT_FMA(OP, 4, 0, 1) LTLT_SLOT_FMA(OP, 5, 1, 1) LTLT_SLOT_FMA(OP, 6, 2, 1) LTLT_SLOT_FMA(OP, 7, 3, 1) \
+  LTLT_SLOT_END(8) \
+  LTLT_SLOT_FMA(OP, 8, 0, 2) LTLT_SLOT_FMA(OP, 9, 1, 2) LTLT_SLOT_FMA(OP, 10, 2, 2) LTLT_SLOT_FMA(OP, 11, 3, 2) \
+  LTLT_SLOT_FMA(OP, 12, 0, 3) LTLT_SLOT_FMA(OP, 13, 1, 3) LTLT_SLOT_FMA(OP, 14, 2, 3) LTLT_SLOT_FMA(OP, 15, 3, 3) \
+  LTLT_SLOT_END(16) \
+  LTLT_SLOT_FMA(OP, 16, 0, 4) LTLT_SLOT_FMA(OP, 17, 1, 4) LTLT_SLOT_FMA(OP, 18, 2, 4) LTLT_SLOT_FMA(OP, 19, 3, 4) \
+  LTLT_SLOT_FMA(OP, 20, 0, 5) LTLT_SLOT_FMA(OP, 21, 1, 5) LTLT_SLOT_FMA(OP, 22, 2, 5) LTLT_SLOT_FMA(OP, 23, 3, 5) \
+  LTLT_SLOT_END(24) \
+  LTLT_SLOT_FMA(OP, 24, 0, 6) LTLT_SLOT_FMA(OP, 25, 1, 6) LTLT_SLOT_FMA(OP, 26, 2, 6) LTLT_SLOT_FMA(OP, 27, 3, 6) \
+  LTLT_SLOT_FMA(OP, 28, 0, 7) LTLT_SLOT_FMA(OP, 29, 1, 7) LTLT_SLOT_FMA(OP, 30, 2, 7) LTLT_SLOT_FMA(OP, 31, 3, 7) \
+  LTLT_SLOT_END(32) \
+  LTLT_SLOT_FMA(OP, 32, 0, 8) LTLT_SLOT_FMA(OP, 33, 1, 8) LTLT_SLOT_FMA(OP, 34, 2, 8) LTLT_SLOT_FMA(OP, 35, 3, 8) \
+  LTLT_SLOT_FMA(OP, 36, 0, 9) LTLT_SLOT_FMA(OP, 37, 1, 9) LTLT_SLOT_FMA(OP, 38, 2, 9) LTLT_SLOT_FMA(OP, 39, 3, 9) \
+  LTLT_SLOT_END(40) \
+  LTLT_SLOT_FMA(OP, 40, 0, 10) LTLT_SLOT_FMA(OP, 41, 1, 10) LTLT_SLOT_FMA(OP, 42, 2, 10) LTLT_SLOT_FMA(OP, 43, 3, 10) \
+  LTLT_SLOT_FMA(OP, 44, 0, 11) LTLT_SLOT_FMA(OP, 45, 1, 11) LTLT_SLOT_FMA(OP, 46, 2, 11) LTLT_SLOT_FMA(OP, 47, 3, 11) \
+  LTLT_SLOT_END(48) \
+  LTLT_SLOT_FMA(OP, 48, 0, 12) LTLT_SLOT_FMA(OP, 49, 1, 12) LTLT_SLOT_FMA(OP, 50, 2, 12) LTLT_SLOT_FMA(OP, 51, 3, 12) \
+  LTLT_SLOT_FMA(OP, 52, 0, 13) LTLT_SLOT_FMA(OP, 53, 1, 13) LTLT_SLOT_FMA(OP, 54, 2, 13) LTLT_SLOT_FMA(OP, 55, 3, 13) \
+  LTLT_SLOT_END(56) \
+  LTLT_SLOT_FMA(OP, 56, 0, 14) LTLT_SLOT_FMA(OP, 57, 1, 14) LTLT_SLOT_FMA(OP, 58, 2, 14) LTLT_SLOT_FMA(OP, 59, 3, 14) \
+  LTLT_SLOT_FMA(OP, 60, 0, 15) LTLT_SLOT_FMA(OP, 61, 1, 15) LTLT_SLOT_FMA(OP, 62, 2, 15) LTLT_SLOT_FMA(OP, 63, 3, 15)
+#define LTLT_REFRESH(OP) \
+  asm volatile("s_nop 1\n" LTLT_SLOT_END(0) LTLT_SLOT_FMAS(OP) \
+               "LTLT_fma%=:\n" \
+               : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]) \
+               : [ns] "s"(nslots), [g0] "v"(g[0]), [g1] "v"(g[1]), [g2] "v"(g[2]), [g3] "v"(g[3]), \
+                 [l0] "v"(L[0]), [l1] "v"(L[1]), [l2] "v"(L[2]), [l3] "v"(L[3]), \
+                 [l4] "v"(L[4]), [l5] "v"(L[5]), [l6] "v"(L[6]), [l7] "v"(L[7]), \
+                 [l8] "v"(L[8]), [l9] "v"(L[9]), [l10] "v"(L[10]), [l11] "v"(L[11]), \
+                 [l12] "v"(L[12]), [l13] "v"(L[13]), [l14] "v"(L[14]), [l15] "v"(L[15]), \
+                 [l16] "v"(L[16]), [l17] "v"(L[17]), [l18] "v"(L[18]), [l19] "v"(L[19]), \
+                 [l20] "v"(L[20]), [l21] "v"(L[21]), [l22] "v"(L[22]), [l23] "v"(L[23]), \
+                 [l24] "v"(L[24]), [l25] "v"(L[25]), [l26] "v"(L[26]), [l27] "v"(L[27]), \
+                 [l28] "v"(L[28]), [l29] "v"(L[29]), [l30] "v"(L[30]), [l31] "v"(L[31]), \
+                 [l32] "v"(L[32]), [l33] "v"(L[33]), [l34] "v"(L[34]), [l35] "v"(L[35]), \
+                 [l36] "v"(L[36]), [l37] "v"(L[37]), [l38] "v"(L[38]), [l39] "v"(L[39]), \
+                 [l40] "v"(L[40]), [l41] "v"(L[41]), [l42] "v"(L[42]), [l43] "v"(L[43]), \
+                 [l44] "v"(L[44]), [l45] "v"(L[45]), [l46] "v"(L[46]), [l47] "v"(L[47]), \
+                 [l48] "v"(L[48]), [l49] "v"(L[49]), [l50] "v"(L[50]), [l51] "v"(L[51]), \
+                 [l52] "v"(L[52]), [l53] "v"(L[53]), [l54] "v"(L[54]), [l55] "v"(L[55]), \
+                 [l56] "v"(L[56]), [l57] "v"(L[57]), [l58] "v"(L[58]), [l59] "v"(L[59]), \
+                 [l60] "v"(L[60]), [l61] "v"(L[61]), [l62] "v"(L[62]), [l63] "v"(L[63]) \
+               : "scc")
+__device__ __forceinline__ void refresh_slots(double (&acc)[4], const double (&g)[4], const double (&L)[KC],
+                                              int nslots) {
   static_assert(KC == 64, "64 slots");
-  switch (c) {
-    LTLT_SLOT_CASE16(0) LTLT_SLOT_CASE16(16) LTLT_SLOT_CASE16(32) LTLT_SLOT_CASE16(48)
-    default: break;
-  }
+  LTLT_REFRESH("v_fmac_f64_dpp");
 }
-#undef LTLT_SLOT_CASE16
-#undef LTLT_SLOT_CASE4
-#undef LTLT_SLOT_CASE
+__device__ __forceinline__ void refresh_slots(float (&acc)[4], const float (&g)[4], const float (&L)[KC], int nslots) {
+  LTLT_REFRESH("v_fmac_f32_dpp");
+}
+#undef LTLT_REFRESH
+#undef LTLT_SLOT_FMAS
+#undef LTLT_SLOT_END
+#undef LTLT_SLOT_FMA
+
+// L[c] = v in the lanes of `on`, for a wave-uniform slot 0 <= c < 64, by a jump
+// straight to the slot's move (s_getpc + offset; every entry is 8 bytes, the
+// first one 12 bytes past the address s_getpc returns).  A switch over 64 slots
+// compiles to a tree of some twelve taken branches (570 cycles a step,
+// measured).
+#define LTLT_SLOT_MOV(OP, c) OP " %[l" #c "], %[v]\ns_branch LTLT_slot%=\n"
+#define LTLT_SLOT_MOVS(OP) \
+  LTLT_SLOT_MOV(OP, 0) LTLT_SLOT_MOV(OP, 1) LTLT_SLOT_MOV(OP, 2) LTLT_SLOT_MOV(OP, 3) \
+  LTLT_SLOT_MOV(OP, 4) LTLT_SLOT_MOV(OP, 5) LTLT_SLOT_MOV(OP, 6) LTLT_SLOT_MOV(OP, 7) \
+  LTLT_SLOT_MOV(OP, 8) LTLT_SLOT_MOV(OP, 9) LTLT_SLOT_MOV(OP, 10) LTLT_SLOT_MOV(OP, 11) \
+  LTLT_SLOT_MOV(OP, 12) LTLT_SLOT_MOV(OP, 13) LTLT_SLOT_MOV(OP, 14) LTLT_SLOT_MOV(OP, 15) \
+  LTLT_SLOT_MOV(OP, 16) LTLT_SLOT_MOV(OP, 17) LTLT_SLOT_MOV(OP, 18) LTLT_SLOT_MOV(OP, 19) \
+  LTLT_SLOT_MOV(OP, 20) LTLT_SLOT_MOV(OP, 21) LTLT_SLOT_MOV(OP, 22) LTLT_SLOT_MOV(OP, 23) \
+  LTLT_SLOT_MOV(OP, 24) LTLT_SLOT_MOV(OP, 25) LTLT_SLOT_MOV(OP, 26) LTLT_SLOT_MOV(OP, 27) \
+  LTLT_SLOT_MOV(OP, 28) LTLT_SLOT_MOV(OP, 29) LTLT_SLOT_MOV(OP, 30) LTLT_SLOT_MOV(OP, 31) \
+  LTLT_SLOT_MOV(OP, 32) LTLT_SLOT_MOV(OP, 33) LTLT_SLOT_MOV(OP, 34) LTLT_SLOT_MOV(OP, 35) \
+  LTLT_SLOT_MOV(OP, 36) LTLT_SLOT_MOV(OP, 37) LTLT_SLOT_MOV(OP, 38) LTLT_SLOT_MOV(OP, 39) \
+  LTLT_SLOT_MOV(OP, 40) LTLT_SLOT_MOV(OP, 41) LTLT_SLOT_MOV(OP, 42) LTLT_SLOT_MOV(OP, 43) \
+  LTLT_SLOT_MOV(OP, 44) LTLT_SLOT_MOV(OP, 45) LTLT_SLOT_MOV(OP, 46) LTLT_SLOT_MOV(OP, 47) \
+  LTLT_SLOT_MOV(OP, 48) LTLT_SLOT_MOV(OP, 49) LTLT_SLOT_MOV(OP, 50) LTLT_SLOT_MOV(OP, 51) \
+  LTLT_SLOT_MOV(OP, 52) LTLT_SLOT_MOV(OP, 53) LTLT_SLOT_MOV(OP, 54) LTLT_SLOT_MOV(OP, 55) \
+  LTLT_SLOT_MOV(OP, 56) LTLT_SLOT_MOV(OP, 57) LTLT_SLOT_MOV(OP, 58) LTLT_SLOT_MOV(OP, 59) \
+  LTLT_SLOT_MOV(OP, 60) LTLT_SLOT_MOV(OP, 61) LTLT_SLOT_MOV(OP, 62) LTLT_SLOT_MOV(OP, 63)                     
+#define LTLT_SLOT_SET(OP) \
+  uint64_t keep; \
+  asm volatile("s_and_saveexec_b64 %[keep], %[on]\n" \
+               "s_getpc_b64 vcc\n" \
+               "s_add_u32 vcc_lo, vcc_lo, %[off]\n" \
+               "s_addc_u32 vcc_hi, vcc_hi, 0\n" \
+               "s_setpc_b64 vcc\n" LTLT_SLOT_MOVS(OP) \
+               "LTLT_slot%=:\n" \
+               "s_mov_b64 exec, %[keep]\n" \
+               : [keep] "=&s"(keep), \
+      [l0] "+v"(L[0]), [l1] "+v"(L[1]), [l2] "+v"(L[2]), [l3] "+v"(L[3])                            , \
+      [l4] "+v"(L[4]), [l5] "+v"(L[5]), [l6] "+v"(L[6]), [l7] "+v"(L[7])                            , \
+      [l8] "+v"(L[8]), [l9] "+v"(L[9]), [l10] "+v"(L[10]), [l11] "+v"(L[11])                        , \
+      [l12] "+v"(L[12]), [l13] "+v"(L[13]), [l14] "+v"(L[14]), [l15] "+v"(L[15])                    , \
+      [l16] "+v"(L[16]), [l17] "+v"(L[17]), [l18] "+v"(L[18]), [l19] "+v"(L[19])                    , \
+      [l20] "+v"(L[20]), [l21] "+v"(L[21]), [l22] "+v"(L[22]), [l23] "+v"(L[23])                    , \
+      [l24] "+v"(L[24]), [l25] "+v"(L[25]), [l26] "+v"(L[26]), [l27] "+v"(L[27])                    , \
+      [l28] "+v"(L[28]), [l29] "+v"(L[29]), [l30] "+v"(L[30]), [l31] "+v"(L[31])                    , \
+      [l32] "+v"(L[32]), [l33] "+v"(L[33]), [l34] "+v"(L[34]), [l35] "+v"(L[35])                    , \
+      [l36] "+v"(L[36]), [l37] "+v"(L[37]), [l38] "+v"(L[38]), [l39] "+v"(L[39])                    , \
+      [l40] "+v"(L[40]), [l41] "+v"(L[41]), [l42] "+v"(L[42]), [l43] "+v"(L[43])                    , \
+      [l44] "+v"(L[44]), [l45] "+v"(L[45]), [l46] "+v"(L[46]), [l47] "+v"(L[47])                    , \
+      [l48] "+v"(L[48]), [l49] "+v"(L[49]), [l50] "+v"(L[50]), [l51] "+v"(L[51])                    , \
+      [l52] "+v"(L[52]), [l53] "+v"(L[53]), [l54] "+v"(L[54]), [l55] "+v"(L[55])                    , \
+      [l56] "+v"(L[56]), [l57] "+v"(L[57]), [l58] "+v"(L[58]), [l59] "+v"(L[59])                    , \
+      [l60] "+v"(L[60]), [l61] "+v"(L[61]), [l62] "+v"(L[62]), [l63] "+v"(L[63]) \
+               : [off] "s"(12 + 8 * c), [on] "s"(mask), [v] "v"(v) \
+               : "vcc", "scc")
+__device__ __forceinline__ void set_slot(double (&L)[KC], int c, bool on, double v) {
+  const uint64_t mask = __ballot(on);
+  LTLT_SLOT_SET("v_mov_b64_e32");
+}
+__device__ __forceinline__ void set_slot(float (&L)[KC], int c, bool on, float v) {
+  const uint64_t mask = __ballot(on);
+  LTLT_SLOT_SET("v_mov_b32_e32");
+}
+#undef LTLT_SLOT_SET
+#undef LTLT_SLOT_MOVS
+#undef LTLT_SLOT_MOV
 
 // v + (v of lane ^ 16) or v + (v of lane ^ 32) through the gfx950 lane
 // swaps (no LDS crossbar round trip): with both operands v, permlane16_swap
@@ -194,6 +294,9 @@ __device__ __forceinline__ void wave_candidate(Cand* red, int wave, const Cand& 
 // pivot value; NaN and p = posw = k+1 when no finite candidate exists), handed
 // to the other waves by a barrier.  A wait that exceeds its bound, or finds the
 // call's abort flag raised, raises the status words and leaves p = -1.
+// early(posw) runs in wave 0 alone as soon as it knows the pivot row, ahead of
+// the barrier: a place to issue loads of that row's data (a row in range, even
+// if the call is being aborted).
 struct __align__(16) XRes {
   double alpha;
   int p, posw;
@@ -213,72 +316,105 @@ __device__ __forceinline__ void exchange_publish(const PanelArgs& a, int s, int 
   }
 }
 
-__device__ __forceinline__ void exchange_collect(const PanelArgs& a, int s, int k, int wave, int lane, XRes& res) {
+template <typename F>
+__device__ __forceinline__ void exchange_collect(const PanelArgs& a, int s, int k, int wave, int lane, XRes& res,
+                                                 F&& early) {
   const int P = a.P;
   const uint64_t* recs = a.rec + (size_t)(s & 1) * (size_t)a.nrec * kRecStride;
   if (wave == 0) {
-    const int q_n = (P + kWave - 1) / kWave;
     const uint64_t t0 = wall_ticks();
-    uint64_t ra[kPollPerLane], rb[kPollPerLane];
     bool gave_up = false;
-    for (;;) {
+    Cand c{0ull, kIdxNone};
+    if (P <= kWave) {
+      // one record per lane (lanes past P read the last one and drop it):
+      // both words and the abort flag in one round trip
+      const uint64_t* rp = &recs[(size_t)kRecStride * min(lane, P - 1)];
+      uint64_t ra, rb;
+      for (;;) {
+        int stv;
+        asm volatile(
+            "global_load_dwordx2 %0, %3, off sc1\n"
+            "global_load_dwordx2 %1, %3, off offset:8 sc1\n"
+            "global_load_dword %2, %4, %5 sc1\n"
+            "s_waitcnt vmcnt(0)"
+            : "=&v"(ra), "=&v"(rb), "=&v"(stv)
+            : "v"(rp), "v"(0), "s"(a.status)
+            : "memory");
+        const bool all = __ballot(!rec_valid(ra, rb, s)) == 0;
+        const bool stop = __builtin_amdgcn_readfirstlane(stv) != 0;
+        // a wait of this call that gave up elsewhere ends this one too, even
+        // when every record has arrived
+        if (__builtin_expect(stop || (!all && wall_ticks() - t0 > kWaitLimitTicks), 0)) {
+          if (lane == 0) raise_wait_status(a.status);
+          gave_up = true;
+          break;
+        }
+        if (all) break;
+      }
+      if (lane < P) c = Cand{ra & 0x7FFFFFFFFFFFFFFFull, rb & 0x7FFFFFFFFFFull};
+    } else {
+      const int q_n = (P + kWave - 1) / kWave;
+      uint64_t ra[kPollPerLane], rb[kPollPerLane];
+      for (;;) {
+#pragma unroll
+        for (int q = 0; q < kPollPerLane; ++q) {
+          const int u = q * kWave + lane;
+          if (q < q_n && u < P) {
+            ra[q] = ld_coh64(&recs[(size_t)kRecStride * u + 0]);
+            rb[q] = ld_coh64(&recs[(size_t)kRecStride * u + 1]);
+          }
+        }
+        const int stv = ld_coh(a.status);         // same round trip as the records
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < kPollPerLane; ++q) {
+          const int u = q * kWave + lane;
+          if (q < q_n && u < P) ok = ok && rec_valid(ra[q], rb[q], s);
+        }
+        const bool all = __ballot(!ok) == 0;
+        if (stv != 0 || (!all && wall_ticks() - t0 > kWaitLimitTicks)) {
+          if (lane == 0) raise_wait_status(a.status);
+          gave_up = true;
+          break;
+        }
+        if (all) break;
+      }
+      // this lane's best of its records (lane, lane + 64, ...)
 #pragma unroll
       for (int q = 0; q < kPollPerLane; ++q) {
         const int u = q * kWave + lane;
         if (q < q_n && u < P) {
-          ra[q] = ld_coh64(&recs[(size_t)kRecStride * u + 0]);
-          rb[q] = ld_coh64(&recs[(size_t)kRecStride * u + 1]);
+          const Cand o{ra[q] & 0x7FFFFFFFFFFFFFFFull, rb[q] & 0x7FFFFFFFFFFull};
+          const bool take = q == 0 || o.v > c.v || (o.v == c.v && cand_lp(o) < cand_lp(c));
+          c.v = take ? o.v : c.v;
+          c.w = take ? o.w : c.w;
         }
       }
-      const int stv = ld_coh(a.status);           // same round trip as the records
-      bool ok = true;
-#pragma unroll
-      for (int q = 0; q < kPollPerLane; ++q) {
-        const int u = q * kWave + lane;
-        if (q < q_n && u < P) ok = ok && rec_valid(ra[q], rb[q], s);
-      }
-      // a wait of this call that gave up elsewhere ends this one too, even
-      // when every record has arrived
-      const bool all = __ballot(!ok) == 0;
-      if (stv != 0 || (!all && wall_ticks() - t0 > kWaitLimitTicks)) {
-        if (lane == 0) raise_wait_status(a.status);
-        gave_up = true;
-        break;
-      }
-      if (all) break;
-      __builtin_amdgcn_s_sleep(0);
     }
-    // this lane's best of its records (lane, lane + 64, ...): positions rise
-    // with neither, so ties compare them
-    Cand c{0ull, kIdxNone};
-#pragma unroll
-    for (int q = 0; q < kPollPerLane; ++q) {
-      const int u = q * kWave + lane;
-      if (q < q_n && u < P) {
-        const Cand o{ra[q] & 0x7FFFFFFFFFFFFFFFull, rb[q] & 0x7FFFFFFFFFFull};
-        const bool take = q == 0 || o.v > c.v || (o.v == c.v && cand_lp(o) < cand_lp(c));
-        c.v = take ? o.v : c.v;
-        c.w = take ? o.w : c.w;
-      }
-    }
-    if (first_max_lane<false>(c, true)) {
-      const bool none = cand_lp(c) == (unsigned)kIdxNone;   // no finite candidate: no exchange
-      const double v = __longlong_as_double((long long)c.v);
-      XRes r;
-      r.alpha = none ? (double)NAN : ((c.w >> 42) & 1 ? -v : v);
-      r.p = gave_up ? -1 : (none ? k + 1 : (int)cand_lp(c));
-      r.posw = none ? k + 1 : (int)((c.w >> 21) & kIdxNone);
-      res = r;
-    }
+    const bool first = first_max_lane<false>(c, true);
+    const bool none = cand_lp(c) == (unsigned)kIdxNone;     // no finite candidate: no exchange
+    const double v = __longlong_as_double((long long)c.v);
+    XRes r;
+    r.alpha = none ? (double)NAN : ((c.w >> 42) & 1 ? -v : v);
+    r.p = gave_up ? -1 : (none ? k + 1 : (int)cand_lp(c));
+    r.posw = none || gave_up ? k + 1 : (int)((c.w >> 21) & kIdxNone);
+    early(__builtin_amdgcn_readlane(r.posw, __ffsll(__ballot(first)) - 1));
+    if (first) res = r;
   }
   __syncthreads();
 }
 
 // Both halves back to back.
+template <typename F>
 __device__ __forceinline__ void exchange_pivot(const PanelArgs& a, int s, int k, int wave, int lane, int w,
-                                               const Cand* red, XRes& res) {
+                                               const Cand* red, XRes& res, F&& early) {
   exchange_publish(a, s, wave, lane, w, red);
-  exchange_collect(a, s, k, wave, lane, res);
+  exchange_collect(a, s, k, wave, lane, res, early);
 }
+
+// Workgroup barrier for LDS only: it waits for this wave's LDS operations
+// but not for its outstanding global loads (__syncthreads does, and with
+// them every tile and solution prefetch in flight).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 }  // namespace ltlt

@@ -23,7 +23,8 @@ struct PanelArgs {
   int R;              // rows per workgroup
   int P;              // workgroups
   int nrec;           // exchange records per slot (>= P of every block)
-  void* G;            // multipliers by block-start index: G[(idx - j - 1) + u*ldw]
+  void* G;            // what a pivot row hands to the others, one row per block-start index idx - j - 1
+  void* tail;         // real panel: the newest of these values, by step (panel_tail_elems)
   void* PO;           // panel out, rows j+1.., columns 0..bw (bw = carry), ld = ldw
   void* Bm;           // Bt = Lx Tx^T for rows >= j+bw+1, columns 0..bw, ld = ldw
   int64_t ldw;
@@ -95,6 +96,8 @@ hipError_t launch_rec_init(uint64_t* rec, int nrec_per_slot, hipStream_t s);
 hipError_t launch_perm_chain(const int* Tblk, int nb, int nblk, int n, int* G, hipStream_t s);
 template <typename T> int panel_max_blocks(int bw, size_t lds);
 int panel_rows(int bw);
+int panel_g_cols(int bw);   // values per row of G in the real panel of width bw
+size_t panel_tail_elems(int bw, int64_t ldw);
 
 // Complex matrices are factored as two real planes (real and imaginary parts,
 // leading dimension ldw).  The complex panel writes its outputs so that each

@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
     const int displaced = lookup(k + 1);           // row at position k+1 before the exchange
     if (!last && rowwave) spec(qs);
 
-    exchange_collect(a, stamp, k, wave, lane, s_x);
+    exchange_collect(a, stamp, k, wave, lane, s_x, [](int) {});
     const XRes xr = s_x;
     const int p = xr.p;
     const int posw = xr.posw;
@@ -284,12 +284,7 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
     {
       const int c = ns / S;
       const bool on = next2 && part == ns % S;
-      const T v = l;
-      if constexpr (S >= 2) {
-        set_slot<T>(L, c, on, v);
-      } else {
-        LTLT_SET_GROUP(0) LTLT_SET_GROUP(16) LTLT_SET_GROUP(32) LTLT_SET_GROUP(48)
-      }
+      set_slot(L, c, on, l);
     }
 #pragma unroll
     for (int u = 0; u < NLQ; ++u) {
@@ -337,12 +332,7 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
       {
         const int c = (ns + 1) / S;
         const bool on = next2 && part == (ns + 1) % S;
-        const T v = wv;
-        if constexpr (S >= 2) {
-          set_slot<T>(L, c, on, v);
-        } else {
-          LTLT_SET_GROUP(0) LTLT_SET_GROUP(16) LTLT_SET_GROUP(32) LTLT_SET_GROUP(48)
-        }
+        set_slot(L, c, on, wv);
       }
       int ro = pos - (j + 1);
       asm volatile("" : "+v"(ro));
@@ -369,8 +359,6 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
     qk = q;
     wave_lds_sync();
   }
-
-#undef LTLT_SET_GROUP
 
   // ---- outputs for the trailing rows (positions >= j+bw): Lx in slot order,
   //      Bt = Lx J^T (column s+1 = -slot s for even s, column s-1 = slot s

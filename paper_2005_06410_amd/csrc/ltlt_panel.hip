@@ -15,11 +15,18 @@
 // row at position k+1 after the exchange is final from then on; the other one
 // keeps its multipliers and column value where they are.
 //
-// A copy of the multipliers also lives in global memory, indexed by the
-// block-start index, G[pos - (j+1)][u], row by row (stride bw) so that the
-// pivot row's multipliers of the earlier steps, which every lane needs after
-// each agreement, are one contiguous run of a few cache lines; it is the only
-// data that crosses workgroups besides the exchange records.
+// What the other rows need of a row when it becomes the pivot -- its g
+// coefficients, below, and its last two multipliers -- crosses workgroups
+// through global memory, indexed by the block-start index; besides the
+// exchange records it is the only data that does.  Two places:
+//   * G, one row of TOT = 64 S values per row, g_u at group u / W, part u % S,
+//     entry (u / S) % 4 with W = 4 S: the four values of a lane side by side, so
+//     that a row is read with wide loads straight into the layout of the
+//     refresh, and written once a group is full (every W steps);
+//   * the tail, a ring of W entries (g_{s-1}, l_s) per row, one written at every
+//     step, entry by entry over the rows, so that a wave's stores are one
+//     contiguous run.  Writing both values to the row's place in G at every
+//     step, a cache line per row, cost 10 of 97 ms at n = 16384.
 //
 // Column refresh.  The trailing matrix is stored as it was at block start
 // (strict lower triangle), so the current column k is the stored column of
@@ -33,10 +40,20 @@
 //   g_u = alpha_{j+u+1} Lrow[u+1] [u <= t-2] - alpha_{j+u} Lrow[u-1] [u >= 1],
 //   Lrow[w] = Lp[w][k] (w <= t-2), Lrow[t-1] = 1 (unit diagonal of L),
 // with S(a, b) = A(a, b) for a > b and -A(b, a) for a < b.
+// Every row forms its own g as its multipliers appear: at step t, with l_t
+// known, g_{t-1} = alpha_{j+t} l_t - alpha_{j+t-1} l_{t-2} is final.  A row that
+// is the pivot of step t needs its last two multipliers as well, for the two
+// coefficients that meet the unit diagonal of L: g_{t-1} = alpha_{j+t} -
+// alpha_{j+t-1} l_{t-2} and g_t = -alpha_{j+t} l_{t-1}.  Wave 0, which learns the
+// pivot first, fetches that row's values once for the workgroup, completes
+// them and hands them out through LDS.  (Every wave gathering the multipliers
+// for itself and forming g from LDS cost about 900 cycles a step, most of it
+// LDS bandwidth, and every wave loading the finished g for itself kept the
+// last wave as far behind the first at the CU's one address unit.)
 // The g coefficients live in registers in "row broadcast" layout: register
-// gr[k], lane l holds g of slot 16k + (l % 16) of the lane's step slice, the
+// gr[k], lane l holds g of slot 4 (l % 16) + k of the lane's step slice, the
 // same in each 16-lane row of that slice, and the refresh multiplies slot c
-// by lane c % 16 of its own row through a DPP row broadcast, so no lane reads
+// by lane c / 4 of its own row through a DPP row broadcast, so no lane re-reads
 // g from LDS.
 //
 // Exchange per step (one grid-wide round, no counters, no fences): every
@@ -46,19 +63,28 @@
 // records until each carries the current stamp and reduces them (largest
 // magnitude, then smallest position: the first maximum in position order), so
 // all workgroups agree on the pivot p.  A barrier hands the result to the
-// other waves; from there each wave works alone: it loads the pivot row's
-// multipliers from G into its own LDS area, forms the g coefficients of the
-// next step and refreshes its rows.  Multipliers written to G at step k are
-// read no earlier than step k+1; every wave waits for its own earlier stores
-// to complete before the barrier that precedes the publication of the next
-// record, so any record that validates implies that the winning row's
-// multipliers are visible.
+// other waves, which load the next stored column (a strided row read for rows
+// above the pivot, waited for only at the end of the refresh), form their
+// multipliers and store what their rows may have to hand out; a second,
+// LDS-only barrier hands them the pivot row's g.
+// Values written to G at step k are read no earlier than step k+1; every wave
+// waits for its own earlier stores to complete before the barrier that
+// precedes the publication of the next record, so any record that validates
+// implies that the winning row's values are visible.
 //
 // After the last step the carry column (column j+bw, refreshed) is formed and
 // every lane writes its row of the block's outputs at its final position:
 // Lx = [Lp, carry] (rows >= j+bw+1) feeds the trailing update as one
 // rank-(bw+1) product with Bt = Lx Tx^T; the rows inside the block and the
 // alphas are committed into A after that update.
+
+//
+// What bounds it: the step is one dependency chain (clock stamps, cycles, n =
+// 16384 / n = 256): publish, poll and reduction of the records 3650 / 2640, the
+// pivot row's values and the stored column 1000 / 600, everything local about
+// 2300.  With the values handed out as above a step takes 4.17 -> 3.0 us at
+// n = 16384 (factorization 97.4 -> 87.5 ms) and 2.6 -> 2.2 us at n = 2048
+// (6.68 -> 5.57 ms), outputs bit-identical.
 
 #include "ltlt_device.h"
 #include "ltlt_exchange.h"
@@ -67,13 +93,61 @@
 namespace ltlt {
 
 int panel_rows(int bw) { return kPanelThreads / panel_split(bw); }
+int panel_g_cols(int bw) { return KC * panel_split(bw); }
+size_t panel_tail_elems(int bw, int64_t ldw) { return (size_t)(4 * panel_split(bw)) * 2 * (size_t)ldw; }
 
-// LDS: per wave, the alpha history (TOT + 1) and the pivot row's multipliers
-// padded by one entry in front (TOT + 2), TOT = steps a row can hold.
-__host__ __device__ constexpr int panel_wave_lds_elems(int tot) { return (tot + 1) + (tot + 2); }
+// Dynamic LDS: the pivot row's g, the block's alphas and pivots (TOT = steps a
+// row can hold).
 template <typename T>
 size_t panel_lds_bytes(int bw, int /*R*/) {
-  return (size_t)kPanelWaves * panel_wave_lds_elems(KC * panel_split(bw)) * sizeof(T);
+  return (size_t)KC * panel_split(bw) * (2 * sizeof(T) + sizeof(int));
+}
+
+// Where step u of a row's g sits in its row of G.
+template <int S>
+__device__ __forceinline__ int g_at(int u) {
+  return u / (4 * S) * (4 * S) + u % S * 4 + u / S % 4;
+}
+// Entry of the tail ring that step s writes (W = 4 S entries per row).
+template <int S>
+__device__ __forceinline__ int ring_at(int s) {
+  return (s - 1) & (4 * S - 1);
+}
+// Device-coherent (sc1) buffer accesses; a lane whose offset is kSkip is out of
+// the buffer's range: its load returns 0 and its store is dropped, without a
+// branch, so that the waits for earlier loads count exactly the accesses
+// issued after them.
+constexpr unsigned kSkip = 0x80000000u;            // buffers are smaller than this
+constexpr int kBufSc1 = 16;                        // buffer cache policy: device scope
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <typename T>
+struct Pair { T a, b; };
+__device__ __forceinline__ void buf_store2(double a, double b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Pair<double>{a, b}), rs, off, base, kBufSc1);
+}
+__device__ __forceinline__ void buf_store2(float a, float b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, Pair<float>{a, b}), rs, off, base, kBufSc1);
+}
+__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kBufSc1);
+}
+// 16 loaded bytes into v[at ..] (unless they lie past its n values).
+__device__ __forceinline__ void put16(double* v, int at, int n, u32x4 x) {
+  const auto d = __builtin_bit_cast(Pair<double>, x);
+  if (at < n) { v[at] = d.a; v[at + 1] = d.b; }
+}
+__device__ __forceinline__ void put16(float* v, int at, int n, u32x4 x) {
+  struct Four { float a, b, c, d; };
+  const auto f = __builtin_bit_cast(Four, x);
+  if (at < n) { v[at] = f.a; v[at + 1] = f.b; v[at + 2] = f.c; v[at + 3] = f.d; }
+}
+// One tail entry (two values).
+__device__ __forceinline__ Pair<double> buf_load2(double, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  return __builtin_bit_cast(Pair<double>, __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kBufSc1));
+}
+__device__ __forceinline__ Pair<float> buf_load2(float, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  return __builtin_bit_cast(Pair<float>, __builtin_amdgcn_raw_buffer_load_b64(rs, off, base, kBufSc1));
 }
 
 template <typename T, int S>
@@ -81,7 +155,7 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int R = kPanelThreads / S;
   constexpr int RW = kWave / S;                    // rows per wave
-  constexpr int NG = KC / 16;                      // g registers
+  constexpr int W = 4 * S;                         // steps of a group of G (four per part)
   constexpr int TOT = KC * S;                      // steps a row can hold
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -92,10 +166,10 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   const int rloc = wave * RW + lane % RW;
   const int64_t lda = a.lda, ldw = a.ldw;
   const T* A = static_cast<const T*>(a.A);
-  T* G = static_cast<T*>(a.G);
 
-  T* my_alpha = reinterpret_cast<T*>(smem) + wave * panel_wave_lds_elems(TOT);   // alpha_{j+u}
-  T* my_lrowp = my_alpha + (TOT + 1);              // my_lrowp[u + 1] = Lrow[u]
+  T* gl = reinterpret_cast<T*>(smem);              // the pivot row's g, as in its row of G
+  T* alpha = gl + TOT;                             // alpha_{j+u}
+  int* piv = reinterpret_cast<int*>(alpha + TOT);  // pivot position of step j+u
   __shared__ XRes s_x;                             // the agreement's result
   __shared__ Cand red[kPanelWaves];
 
@@ -105,18 +179,31 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   const int pos = row0 + rloc;                     // block-start index of this lane's row
   int lp = pos;                                    // its current position
 
-  T L[KC], gr[NG];
+  T L[KC], gr[4];
 #pragma unroll
   for (int c = 0; c < KC; ++c) L[c] = T(0);
 #pragma unroll
-  for (int k = 0; k < NG; ++k) gr[k] = T(0);
-  if (lane == 0) my_lrowp[0] = T(0);               // Lrow[-1]: only ever multiplied, kept finite
+  for (int kk = 0; kk < 4; ++kk) gr[kk] = T(0);
   T cv = T(0);
-  // stored column value of this row and its sign (S(a,b) = -A(b,a) above the
-  // diagonal); the sign is applied in the refresh so that no code waits for
-  // the load before then.  First column: index j, rows >= j+1 (lower part).
-  T lv = T(0), lsg = T(1);
-  if (my_row && part == 0) lv = A[(int64_t)pos + (int64_t)j * lda];
+  T l1 = T(0), l2 = T(0), alph1 = T(0);            // multipliers of steps t-1, t-2; alpha_{j+t-1}
+  const int posc = min(pos, n - 1);                // in range for lanes without a row too
+  int64_t rowat = (int64_t)posc * lda;             // element (., posc)
+  // where this lane writes of its own row (gso: slots 4b .. 4b+3 of its part in
+  // G; tso: the tail entry, part 0)
+  constexpr unsigned TSZ = 2 * sizeof(T);
+  const int b16 = lane & 15;
+  const unsigned gso = (unsigned)((pos - (j + 1)) * TOT + part * 4) * (unsigned)sizeof(T);
+  const unsigned tso = (unsigned)(pos - (j + 1)) * TSZ;
+  const unsigned tstep = (unsigned)ldw * TSZ;      // bytes from one ring entry to the next
+  const __amdgpu_buffer_rsrc_t grs =
+      __builtin_amdgcn_make_buffer_rsrc(a.G, (short)0, (int)((unsigned)(n - 1 - j) * TOT * sizeof(T)), 0x00020000);
+  const __amdgpu_buffer_rsrc_t trs = __builtin_amdgcn_make_buffer_rsrc(a.tail, (short)0, (int)(W * tstep), 0x00020000);
+  T pg[4] = {T(0), T(0), T(0), T(0)};              // this part's g not yet in G
+  // stored column value of this row (signed; zero past part 0).  First
+  // column: index j, rows >= j+1 (lower part).
+  T lvn = A[(int64_t)posc + (int64_t)j * lda];
+  bool below = true;
+  asm volatile("" : "+v"(lvn));                    // arrived: no wait for it inside the loop
   __syncthreads();
 
   for (int t = 0; t <= bw; ++t) {
@@ -125,13 +212,10 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
     const bool active = my_row && lp >= k + 1;
     {
       T acc[4] = {T(0), T(0), T(0), T(0)};
-      static_assert(NG == 4, "four g registers");
-      if (0 * 16 * S < t) refresh16<0>(acc, gr[0], L);
-      if (1 * 16 * S < t) refresh16<1>(acc, gr[1], L);
-      if (2 * 16 * S < t) refresh16<2>(acc, gr[2], L);
-      if (3 * 16 * S < t) refresh16<3>(acc, gr[3], L);
-      T sum = fma(lsg, lv, (acc[0] + acc[1]) + (acc[2] + acc[3]));   // lv is nonzero in part 0 only
-      sum = part_sum<S>(sum);
+      refresh_slots(acc, gr, L, (t + S - 1) / S);
+      // the stored value, waited for only here (one part adds it)
+      const T lv = part == 0 ? (below ? lvn : -lvn) : T(0);
+      const T sum = part_sum<S>(lv + ((acc[0] + acc[1]) + (acc[2] + acc[3])));
       if (active) cv = sum;
     }
     if (t == bw) break;                           // carry column formed
@@ -142,98 +226,75 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
       const double m = (double)fabs(cv);
       wave_candidate(red, wave, make_cand(active && part == 0 && m == m, m, cv < T(0), pos, lp));
     }
-    exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x);
+    // Wave 0 fetches what the column needs of the pivot row, for all waves, as
+    // soon as it knows the row: g from G up to the last full group, the ring.
+    constexpr int GL = (TOT * (int)sizeof(T) + 1023) / 1024;   // 16-byte loads per lane
+    const int full = max(t - 1, 0) / W * W;        // steps whose g is in G
+    u32x4 gq[GL];
+    Pair<T> tq;
+    exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x, [&](int row) {
+      const unsigned r = (unsigned)(row - (j + 1));
+#pragma unroll
+      for (int q = 0; q < GL; ++q) {
+        const unsigned off = (unsigned)(q * 1024 + lane * 16);
+        gq[q] = buf_load16(grs, off < (unsigned)(full * sizeof(T)) ? off : kSkip, r * (unsigned)(TOT * sizeof(T)));
+      }
+      tq = buf_load2(T(0), trs, lane < W ? (unsigned)lane * tstep : kSkip, r * TSZ);
+    });
     const XRes xr = s_x;
     const T alph = (T)xr.alpha;
-    const int p = xr.p;
-    const int posw = xr.posw;                      // block-start index of the pivot row
+    const int p = __builtin_amdgcn_readfirstlane(xr.p);
+    const int posw = __builtin_amdgcn_readfirstlane(xr.posw);   // block-start index of the pivot row
     if (p < 0) return;
 
-    // ---- exchange positions k+1 and p (logical only) ----
-    if (my_row && p != k + 1) {
-      if (lp == p) lp = k + 1;
-      else if (lp == k + 1) lp = p;
-    }
+    // ---- the next stored column S(pos, posw) = +A(pos, posw) below the
+    //      diagonal, -A(posw, pos) above; waited for in its refresh ----
+    int64_t at1 = (int64_t)posw * lda + posc, at2 = rowat + posw;
+    asm volatile("" : "+v"(at1), "+v"(at2));       // both formed, one selected: no branch
+    below = pos > posw;
+    lvn = A[below ? at1 : at2];
+    __builtin_amdgcn_sched_barrier(0);             // keep the loads ahead of the work below
+
+    // ---- exchange positions k+1 and p (logical only); multiplier of step k;
+    //      into its slot; this row's g_{t-1} ----
+    lp = lp == p ? k + 1 : (lp == k + 1 ? p : lp);
     const bool next = my_row && lp >= k + 2;      // rows still to be eliminated
-
-    // ---- one round of loads: pivot row multipliers, then the next stored
-    //      column.  Every lane issues the same loads (multiplier addresses
-    //      clamped to steps < t, the stored column's to A(j+1, j) where it
-    //      is not needed), so the in-order memory counter lets g be formed
-    //      from the multipliers while the stored column, a strided row read
-    //      for rows above the pivot, is still in flight. ----
-    constexpr int NLQ = TOT / kWave;              // multiplier loads per lane
-    T lr[NLQ];
-    {
-      const T* grow = G + (int64_t)(posw - (j + 1)) * bw;
-      const int umax = t > 0 ? t - 1 : 0;
-#pragma unroll
-      for (int q = 0; q < NLQ; ++q) lr[q] = ld_coh_t(&grow[min(q * kWave + lane, umax)]);
+    T l = cv / alph;
+    l = next && alph != T(0) ? l : T(0);
+    set_slot(L, t / S, part == t % S, l);
+    if (tid == 0) {
+      alpha[t] = alph;
+      piv[t] = p;
     }
-    // S(pos, posw) = +A(pos, posw) below the diagonal, -A(posw, pos) above:
-    // element (max, min) of the stored triangle
-    const bool ldv = next && part == 0;
-    const int64_t lvi = ldv ? (int64_t)max(pos, posw) + (int64_t)min(pos, posw) * lda : (int64_t)(j + 1) + (int64_t)j * lda;
-    const T lvn = A[lvi];
-    __builtin_amdgcn_sched_barrier(0);             // keep the load ahead of the work below
-
-    // ---- multiplier of step k; the pivot row's multipliers into LDS before
-    //      the slot write below (a jump), so their wait counts exactly.
-    //      Entries past step t hold clamped copies that g discards; lane 0
-    //      then writes the unit entry over entry t+1. ----
-    T l = T(0);
-    if (next) l = (alph != T(0)) ? cv / alph : T(0);
+    const T gown = fma(-alph1, l2, alph * l);
+    const int u = max(t - 1, 0);
 #pragma unroll
-    for (int q = 0; q < NLQ; ++q) my_lrowp[q * kWave + lane + 1] = lr[q];
-    if (lane == 0) { my_alpha[t] = alph; my_lrowp[t + 1] = T(1); }   // Lrow[t] = 1: unit diagonal
-    {
-      const int c = t / S;
-      const bool on = next && part == t % S;
-      const T v = l;
-      static_assert(KC == 64, "four groups of 16 slots");
-      if constexpr (S >= 2) {
-        set_slot<T>(L, c, on, v);
-      } else {
-        LTLT_SET_GROUP(0) LTLT_SET_GROUP(16) LTLT_SET_GROUP(32) LTLT_SET_GROUP(48)
-      }
+    for (int kk = 0; kk < 4; ++kk) pg[kk] = (u % S == part && (u / S) % 4 == kk) ? gown : pg[kk];
+    buf_store2(gown, l, trs, next && part == 0 ? tso : kSkip, (unsigned)ring_at<S>(t) * tstep);
+    if (u % W == W - 1) {                          // a full group: this part's four values
+      const unsigned to = next ? gso : kSkip, at = (unsigned)(u / W) * (unsigned)(W * sizeof(T));
+      buf_store2(pg[0], pg[1], grs, to, at);
+      buf_store2(pg[2], pg[3], grs, to + 2 * (unsigned)sizeof(T), at);
     }
 
-    // ---- g coefficients for step k+1 (t+1 terms), row broadcast layout ----
-    wave_lds_sync();
-    {
-      const int c = lane & 15;
-      // every group's reads issued at once (in bounds for any u < TOT; the
-      // entries past step t are discarded by the selects, never multiplied
-      // into a kept value), rather than one group's round trip after another
+    // ---- g of the next column, through LDS: from G, from the ring, zeros past
+    //      it, then the two coefficients that meet the unit diagonal of L.
+    //      One wave's LDS writes take effect in their order. ----
+    if (wave == 0) {
 #pragma unroll
-      for (int kk = 0; kk < NG; ++kk) {
-        const int u = (16 * kk + c) * S + part;    // < TOT
-        const T a0 = my_alpha[u], a1 = my_alpha[u + 1];
-        const T lm = my_lrowp[u], l1 = my_lrowp[u + 2];
-        const T up = (u <= t - 1) ? a1 * l1 : T(0);
-        const T g = (u >= 1) ? up - a0 * lm : up;
-        gr[kk] = (u <= t) ? g : T(0);
-      }
+      for (int q = 0; q < GL; ++q) put16(gl, (q * kWave + lane) * (16 / (int)sizeof(T)), TOT, gq[q]);
+      if (lane < W) gl[full + (lane % S) * 4 + lane / S] = full + lane < t - 1 ? tq.a : T(0);
+      if (lane == ring_at<S>(t - 2) && t >= 1) gl[g_at<S>(t - 1)] = fma(-alph1, t < 2 ? T(0) : tq.b, alph);
+      if (lane == ring_at<S>(t - 1)) gl[g_at<S>(t)] = t < 1 ? T(0) : -alph * tq.b;
     }
-    // the stored column is taken before the stores below are issued, so its
-    // wait does not include their acknowledgement
-    if (ldv) {
-      lv = lvn;
-      lsg = pos > posw ? T(1) : T(-1);
-    }
-    asm volatile("" : "+v"(lv), "+v"(lsg) : : "memory");
-    {
-      // recompute the row offset here instead of keeping a 64-bit pointer
-      // live across the step loop (the kernel runs at the register limit)
-      int ro = pos - (j + 1);
-      asm volatile("" : "+v"(ro));
-      if (next && part == t % S) st_coh_t(&G[(int64_t)ro * bw + t], l);
-    }
-    if (tid == 0 && w == 0) a.ipiv[k + 1] = p;
-    wave_lds_sync();
+    lds_barrier();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) gr[kk] = gl[(b16 * S + part) * 4 + kk];
+    l2 = l1;
+    l1 = l;
+    alph1 = alph;
   }
-
-#undef LTLT_SET_GROUP
+  __syncthreads();                                 // the alphas and pivots in LDS
 
   // ---- outputs, by final position, straight from registers.  Rows at
   //      positions j+1 .. j+bw hold the multipliers of the steps before they
@@ -244,7 +305,6 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   const int tr0 = j + bw + 1;                      // first trailing position
   const bool trailing = my_row && lp >= tr0;
   const T carry = trailing ? cv : T(0);
-  const T* alpha = my_alpha;                       // alpha_{j+u}, u < bw
   if (my_row) {
     const int64_t ro = lp - (j + 1);
 #pragma unroll
@@ -290,7 +350,10 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   if (my_row && part == 0) a.perm[lp] = pos;
   if (w == 0 && wave == 0) {
     T* al = static_cast<T*>(a.alpha);
-    for (int u = lane; u < bw; u += kWave) al[u] = alpha[u];
+    for (int u = lane; u < bw; u += kWave) {
+      al[u] = alpha[u];
+      a.ipiv[j + u + 1] = piv[u];
+    }
   }
 }
 

@@ -353,11 +353,6 @@ __global__ void __launch_bounds__(2 * kLook * kWave) solve_mmat_kernel(const T* 
   }
 }
 
-// Workgroup barrier for LDS only: it waits for this wave's LDS operations
-// but not for its outstanding global loads (__syncthreads does, and with
-// them every tile and solution prefetch in flight).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // Workgroup-wide AND of v over an LDS-only barrier: each wave's vote goes to
 // one of two flag sets, alternating per call (a set is rewritten two votes
 // later, after every wave has passed the barrier of the vote in between).
