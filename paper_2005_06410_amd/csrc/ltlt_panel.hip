@@ -113,24 +113,30 @@ template <int S>
 __device__ __forceinline__ int ring_at(int s) {
   return (s - 1) & (4 * S - 1);
 }
-// Device-coherent (sc1) buffer accesses; a lane whose offset is kSkip is out of
+// Buffer accesses; a lane whose offset is kSkip is out of
 // the buffer's range: its load returns 0 and its store is dropped, without a
 // branch, so that the waits for earlier loads count exactly the accesses
 // issued after them.
 constexpr unsigned kSkip = 0x80000000u;            // buffers are smaller than this
-constexpr int kBufSc1 = 16;                        // buffer cache policy: device scope
+// Buffer cache policy: device scope (sc1) between workgroups; within one, whose
+// waves share a CU and its L1, plain accesses (L2 hits instead of trips past it).
+template <bool ONE>
+constexpr int kPolicy = ONE ? 0 : 16;
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 template <typename T>
 struct Pair { T a, b; };
+template <bool ONE>
 __device__ __forceinline__ void buf_store2(double a, double b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Pair<double>{a, b}), rs, off, base, kBufSc1);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Pair<double>{a, b}), rs, off, base, kPolicy<ONE>);
 }
+template <bool ONE>
 __device__ __forceinline__ void buf_store2(float a, float b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, Pair<float>{a, b}), rs, off, base, kBufSc1);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, Pair<float>{a, b}), rs, off, base, kPolicy<ONE>);
 }
+template <bool ONE>
 __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  return __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kBufSc1);
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kPolicy<ONE>);
 }
 // 16 loaded bytes into v[at ..] (unless they lie past its n values).
 __device__ __forceinline__ void put16(double* v, int at, int n, u32x4 x) {
@@ -143,14 +149,17 @@ __device__ __forceinline__ void put16(float* v, int at, int n, u32x4 x) {
   if (at < n) { v[at] = f.a; v[at + 1] = f.b; v[at + 2] = f.c; v[at + 3] = f.d; }
 }
 // One tail entry (two values).
+template <bool ONE>
 __device__ __forceinline__ Pair<double> buf_load2(double, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  return __builtin_bit_cast(Pair<double>, __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kBufSc1));
+  return __builtin_bit_cast(Pair<double>, __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kPolicy<ONE>));
 }
+template <bool ONE>
 __device__ __forceinline__ Pair<float> buf_load2(float, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  return __builtin_bit_cast(Pair<float>, __builtin_amdgcn_raw_buffer_load_b64(rs, off, base, kBufSc1));
+  return __builtin_bit_cast(Pair<float>, __builtin_amdgcn_raw_buffer_load_b64(rs, off, base, kPolicy<ONE>));
 }
 
-template <typename T, int S>
+// ONE: one workgroup holds every row (a.P == 1).
+template <typename T, int S, bool ONE>
 __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int R = kPanelThreads / S;
@@ -171,8 +180,9 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   T* alpha = gl + TOT;                             // alpha_{j+u}
   int* piv = reinterpret_cast<int*>(alpha + TOT);  // pivot position of step j+u
   __shared__ XRes s_x;                             // the agreement's result
-  __shared__ Cand red[kPanelWaves];
+  __shared__ Cand red[ONE ? 2 * kPanelWaves : kPanelWaves];
 
+  if (ONE && ld_coh(a.status) != 0) return;        // the call has already failed
   const int row0 = j + 1 + w * R;                 // first block-start index held
   const int rows_here = max(0, min(R, n - row0));
   const bool my_row = rloc < rows_here;
@@ -222,9 +232,10 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
 
     // ---- this wave's pivot candidate: (|cv|, position), first maximum; one
     //      lane per row, NaN is never a candidate ----
+    Cand* wred = ONE ? red + (t & 1) * kPanelWaves : red;
     {
       const double m = (double)fabs(cv);
-      wave_candidate(red, wave, make_cand(active && part == 0 && m == m, m, cv < T(0), pos, lp));
+      wave_candidate(wred, wave, make_cand(active && part == 0 && m == m, m, cv < T(0), pos, lp));
     }
     // Wave 0 fetches what the column needs of the pivot row, for all waves, as
     // soon as it knows the row: g from G up to the last full group, the ring.
@@ -232,16 +243,22 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
     const int full = max(t - 1, 0) / W * W;        // steps whose g is in G
     u32x4 gq[GL];
     Pair<T> tq;
-    exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x, [&](int row) {
+    auto fetch = [&](int row) {
       const unsigned r = (unsigned)(row - (j + 1));
 #pragma unroll
       for (int q = 0; q < GL; ++q) {
         const unsigned off = (unsigned)(q * 1024 + lane * 16);
-        gq[q] = buf_load16(grs, off < (unsigned)(full * sizeof(T)) ? off : kSkip, r * (unsigned)(TOT * sizeof(T)));
+        gq[q] = buf_load16<ONE>(grs, off < (unsigned)(full * sizeof(T)) ? off : kSkip, r * (unsigned)(TOT * sizeof(T)));
       }
-      tq = buf_load2(T(0), trs, lane < W ? (unsigned)lane * tstep : kSkip, r * TSZ);
-    });
-    const XRes xr = s_x;
+      tq = buf_load2<ONE>(T(0), trs, lane < W ? (unsigned)lane * tstep : kSkip, r * TSZ);
+    };
+    XRes xr;
+    if constexpr (ONE) {
+      xr = exchange_one(k, wave, lane, wred, fetch);
+    } else {
+      exchange_pivot(a, k + 1, k, wave, lane, w, red, s_x, fetch);
+      xr = s_x;
+    }
     const T alph = (T)xr.alpha;
     const int p = __builtin_amdgcn_readfirstlane(xr.p);
     const int posw = __builtin_amdgcn_readfirstlane(xr.posw);   // block-start index of the pivot row
@@ -270,11 +287,11 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
     const int u = max(t - 1, 0);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) pg[kk] = (u % S == part && (u / S) % 4 == kk) ? gown : pg[kk];
-    buf_store2(gown, l, trs, next && part == 0 ? tso : kSkip, (unsigned)ring_at<S>(t) * tstep);
+    buf_store2<ONE>(gown, l, trs, next && part == 0 ? tso : kSkip, (unsigned)ring_at<S>(t) * tstep);
     if (u % W == W - 1) {                          // a full group: this part's four values
       const unsigned to = next ? gso : kSkip, at = (unsigned)(u / W) * (unsigned)(W * sizeof(T));
-      buf_store2(pg[0], pg[1], grs, to, at);
-      buf_store2(pg[2], pg[3], grs, to + 2 * (unsigned)sizeof(T), at);
+      buf_store2<ONE>(pg[0], pg[1], grs, to, at);
+      buf_store2<ONE>(pg[2], pg[3], grs, to + 2 * (unsigned)sizeof(T), at);
     }
 
     // ---- g of the next column, through LDS: from G, from the ring, zeros past
@@ -359,7 +376,8 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
 
 template <typename T, int S>
 hipError_t launch_panel_s(const PanelArgs& a, size_t lds, hipStream_t st) {
-  return launch_resident_grid(panel_kernel<T, S>, (unsigned)a.P, kPanelThreads, lds, st, a);
+  if (a.P == 1) return launch_resident_grid(panel_kernel<T, S, true>, 1u, kPanelThreads, lds, st, a);
+  return launch_resident_grid(panel_kernel<T, S, false>, (unsigned)a.P, kPanelThreads, lds, st, a);
 }
 
 template <typename T>
@@ -378,7 +396,7 @@ int panel_max_blocks_s(size_t lds) {
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)panel_kernel<T, S>, kPanelThreads, lds) !=
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)panel_kernel<T, S, false>, kPanelThreads, lds) !=
       hipSuccess)
     return 0;
   return per_cu * cus;
