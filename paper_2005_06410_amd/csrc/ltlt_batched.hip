@@ -32,20 +32,29 @@
 // Global traffic is one read and one write of each strict lower triangle,
 // plus ipiv and the Pfaffian, which is what bounds this path (HBM).
 
+#include <type_traits>
+
 #include "ltlt_device.h"
 #include "ltlt_internal.h"
 
 namespace ltlt {
 
-constexpr int kBN = 64;                          // largest order handled
-constexpr int kBSlots = 64;                      // multiplier slots per lane (steps 0..61)
+constexpr int kBMaxN = 64;                       // largest order handled
 constexpr int kBBlk = 16;                        // column steps per block
-constexpr int kBPack = kBN * (kBN - 1) / 2;      // packed strict lower triangle
-constexpr int kBAlpha = kBSlots + 2;             // alpha history (even length keeps the next array 16-byte aligned)
 constexpr int kBRow = kBBlk + 2;                 // pivot row's in-block multipliers and its unit
-constexpr int kBPiv = kBN + 4;                   // ipiv entries 0..64 (steps past n-2 write up to entry 64)
-constexpr int kBWaveLds = kBPack + kBAlpha + kBRow + kBPiv + kBN;   // + ipiv and the trailing-row table (ints)
 constexpr int kBWaves = 4;                       // matrices per workgroup
+
+// Sizes of the kernel for orders up to NB (16, 32, 48 or 64): multiplier slots
+// per lane, packed strict lower triangle, alpha history (even length keeps the
+// next array 16-byte aligned), ipiv entries (steps past n-2 write up to entry
+// NB) and the trailing-row table.
+template <int NB>
+struct BSize {
+  static constexpr int pack = NB * (NB - 1) / 2;
+  static constexpr int alpha = NB + 2;
+  static constexpr int piv = NB + 4;
+  static constexpr int wave = pack + alpha + kBRow + piv + 64;   // elements of LDS per wave
+};
 
 // Offset of X(i, c), i > c, in the column-packed strict lower triangle:
 // col_off(n, c) + i.
@@ -164,13 +173,64 @@ __device__ __forceinline__ void update_group(T* orig, int n, int pos, bool ta, i
     if (ok[j]) orig[idx[j]] = a[j];
 }
 
-// Waves per SIMD: fp64 two (the packed triangle takes 17.8 KB of LDS per
-// matrix, and the registers fill 256 VGPRs); fp32 four, by capping it at 128
-// VGPRs (a few values then live in scratch, which still beats three waves).
-template <typename T>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) batched_kernel(int n, int batch, T* Aall, int64_t lda, int64_t strideA,
-                                                         int* ipiv_all, int64_t strideIpiv, double* logabs,
-                                                         int* sign) {
+// First maximum of |cv| by position over the lanes of `on` (none holds a NaN):
+// its lane, or -1 without any; keys are compared in the value's own width (the
+// high words of doubles first), ties resolved by two more reductions.
+__device__ __forceinline__ int pivot_lane(bool on, float cv, int lp) {
+  const unsigned hk = on ? (__float_as_uint(cv) & 0x7FFFFFFFu) + 1u : 0u;
+  const unsigned mh = wave_umax(hk);
+  unsigned long long b = __ballot(hk == mh);
+  if (__builtin_expect((b & (b - 1)) != 0, 0)) {
+    if (mh == 0) return -1;
+    const unsigned nk = hk == mh ? ~(unsigned)lp : 0u;
+    b = __ballot(nk == wave_umax(nk));
+  }
+  return __ffsll(b) - 1;
+}
+__device__ __forceinline__ int pivot_lane(bool on, double cv, int lp) {
+  const unsigned hk = on ? ((unsigned)__double2hiint(cv) & 0x7FFFFFFFu) + 1u : 0u;
+  const unsigned mh = wave_umax(hk);
+  unsigned long long b = __ballot(hk == mh);
+  if (__builtin_expect((b & (b - 1)) != 0, 0)) {
+    if (mh == 0) return -1;
+    const unsigned lo = (unsigned)__double2loint(cv);
+    const unsigned ml = wave_umax(hk == mh ? lo : 0u);
+    const unsigned nk = hk == mh && lo == ml ? ~(unsigned)lp : 0u;
+    b = __ballot(nk == wave_umax(nk));
+  }
+  return __ffsll(b) - 1;
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// Waves per SIMD that the registers are capped for.  fp64 order 64: two (the
+// packed triangle takes 17.8 KB of LDS per matrix); elsewhere as many as spill
+// little: with 5000 matrices of order 22, fp64 takes 63.6 us uncapped (two
+// waves), 53.4 at three, 58.8 at four; fp32 41.3 at four, 37.4 at six; of order
+// 48, fp64 147.7, 141.7 and 163.4 us at two, three and four, fp32 91.4 at four
+// and 93.4 at six.
+template <typename T, int NB>
+constexpr int batched_waves() {
+  return sizeof(T) == 8 ? (NB <= 16 ? 4 : NB <= 48 ? 3 : 2) : (NB <= 16 ? 8 : NB <= 32 ? 6 : 4);
+}
+
+// One instance per order range: a step's cost hardly depends on the order, so
+// what counts for small matrices is how many waves share a SIMD, and that the
+// registers and LDS of order 64 set.  Against the one instance for every
+// order: 5000 matrices of order 16 in fp64 53.3 -> 28.2 us, order 22 87.7 -> 53.4
+// (fp32 57.2 -> 37.4), order 32 102 -> 74, 8192 of order 64 in fp64 303 -> 281
+// (shorter pivot search alone); outputs bit-identical.
+template <typename T, int NB>
+__global__ void __launch_bounds__(256, (batched_waves<T, NB>()))
+    batched_kernel(int n, int batch, T* Aall, int64_t lda, int64_t strideA, int* ipiv_all, int64_t strideIpiv,
+                   double* logabs, int* sign) {
+  constexpr int kBWaveLds = BSize<NB>::wave, kBPack = BSize<NB>::pack, kBAlpha = BSize<NB>::alpha,
+                kBPiv = BSize<NB>::piv, kBSlots = NB;
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
@@ -187,19 +247,14 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) batched_kernel(in
   // strict lower triangle into LDS.  Column c holds n-1-c < 64 entries, one
   // per lane (coalesced); the loads of all columns are issued before any of
   // them is written, so a matrix costs one memory round trip.
-  constexpr int kBFill = kBN;
-  for (int c0 = 0; c0 + 1 < n; c0 += kBFill) {
-    T v[kBFill];
+  {
+    T v[NB];
 #pragma unroll
-    for (int cc = 0; cc < kBFill; ++cc) {
-      const int c = c0 + cc;
-      v[cc] = (c + 1 < n && lane < n - 1 - c) ? A[(int64_t)(c + 1 + lane) + (int64_t)c * lda] : T(0);
-    }
+    for (int c = 0; c < NB; ++c)
+      v[c] = (c + 1 < n && lane < n - 1 - c) ? A[(int64_t)(c + 1 + lane) + (int64_t)c * lda] : T(0);
 #pragma unroll
-    for (int cc = 0; cc < kBFill; ++cc) {
-      const int c = c0 + cc;
-      if (c + 1 < n && lane < n - 1 - c) orig[pack_idx(n, c + 1, c) + lane] = v[cc];
-    }
+    for (int c = 0; c < NB; ++c)
+      if (c + 1 < n && lane < n - 1 - c) orig[pack_idx(n, c + 1, c) + lane] = v[c];
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 
@@ -217,14 +272,16 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) batched_kernel(in
   T lv = my_row ? orig[pack_idx(n, pos, 0)] : T(0), lsg = T(1);   // column 0: S(pos, 0)
   int npiv = 0;                                    // exchanges made (Pfaffian sign)
 
-  // Every block runs all 16 steps: a step with k + 2 >= n has at most the
+  // Every block runs all 8 or 16 steps: a step with k + 2 >= n has at most the
   // row at position n-1 as candidate and no row below it, so it forms alpha_k
   // (k = n-2) or nothing, exchanges nothing and leaves every multiplier 0;
   // its alpha and pivot entries past n-2 are never read.
   int k0 = 0;
   while (k0 + 1 < n) {
+    auto steps8 = [&](auto half) {
 #pragma unroll
-    for (int tt = 0; tt < kBBlk; ++tt) {          // step k = k0 + tt
+    for (int t8 = 0; t8 < 8; ++t8) {              // step k = k0 + tt
+      const int tt = 8 * decltype(half)::value + t8;
       const int k = k0 + tt;
       const bool active = my_row && lp >= k + 1;
       if (tt > 0 || k0 == 0) {                    // a block's first column is the carry of the block before
@@ -235,20 +292,12 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) batched_kernel(in
         if (active) cv = sum;
       }
       // pivot: first maximum of |cv| by position (NaN never a candidate)
-      double av = -1.0;
-      if (active) {
-        const double mag = (double)fabs(cv);
-        if (mag == mag) av = mag;
-      }
-      double vmax;
-      int p;
-      const int wl = wave_first_max(av, active ? lp : INT32_MAX, vmax, p);
+      const int wl = pivot_lane(active && cv == cv, cv, lp);
       // no finite candidate (wl < 0): no exchange, alpha NaN
       const int wsrc = wl < 0 ? 0 : wl;
-      const int posw = wl < 0 ? k + 1 : __builtin_amdgcn_readlane(pos, wsrc);
-      const int wneg = __builtin_amdgcn_readlane(cv < T(0) ? 1 : 0, wsrc);
-      const T alph = wl < 0 ? T(NAN) : (wneg ? -(T)vmax : (T)vmax);
-      if (wl < 0) p = k + 1;
+      const int posw = wl < 0 ? k + 1 : wl + 1;
+      const int p = wl < 0 ? k + 1 : __builtin_amdgcn_readlane(lp, wsrc);
+      const T alph = wl < 0 ? T(NAN) : lane_value(cv, wsrc);
       my_alpha[k] = alph;                          // uniform values, stored by every lane
       my_piv[k + 1] = p;                           // k + 1 <= 64 < kBPiv
       npiv += p != k + 1 ? 1 : 0;
@@ -287,8 +336,11 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) batched_kernel(in
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
+    };
+    steps8(std::integral_constant<int, 0>());
+    if (k0 + 9 < n) steps8(std::integral_constant<int, 1>());   // else no step is left
     const int kn = k0 + kBBlk;                     // first step of the next block
-    if (kn + 1 >= n) break;
+    if (NB <= kBBlk || kn + 1 >= n) break;         // the last block
     // the carry: column kn refreshed with all of this block's steps
     const bool ta = my_row && lp >= kn + 1;        // rows still to be eliminated
     {
@@ -333,8 +385,8 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) batched_kernel(in
     }
     // archive the block's multipliers
 #define LTLT_ARCHIVE(B)                                                   \
-    if (k0 == 16 * B) {                                                   \
-      _Pragma("unroll") for (int u = 0; u < kBBlk; ++u) L[16 * B + u] = Lb[u]; \
+    if (16 * B < NB && k0 == 16 * B) {                                    \
+      _Pragma("unroll") for (int u = 0; u < kBBlk; ++u) L[16 * B < NB ? 16 * B + u : 0] = Lb[u]; \
     }
     LTLT_ARCHIVE(0) LTLT_ARCHIVE(1) LTLT_ARCHIVE(2) LTLT_ARCHIVE(3)
 #pragma unroll
@@ -386,17 +438,26 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) batched_kernel(in
   }
 }
 
+template <typename T, int NB>
+hipError_t launch_batched_n(int n, int batch, T* A, int64_t lda, int64_t strideA, int* ipiv, int64_t strideIpiv,
+                            double* logabs, int* sign, hipStream_t s) {
+  const size_t lds = (size_t)kBWaves * BSize<NB>::wave * sizeof(T);
+  const hipError_t e = ensure_dynamic_lds((const void*)batched_kernel<T, NB>, (int)lds);
+  if (e != hipSuccess) return e;
+  const int grid = (batch + kBWaves - 1) / kBWaves;
+  hipLaunchKernelGGL((batched_kernel<T, NB>), dim3(grid), dim3(256), lds, s, n, batch, A, lda, strideA, ipiv,
+                     strideIpiv, logabs, sign);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_batched(int n, int batch, T* A, int64_t lda, int64_t strideA, int* ipiv, int64_t strideIpiv,
                           double* logabs, int* sign, hipStream_t s) {
   if (batch <= 0) return hipSuccess;
-  const size_t lds = (size_t)kBWaves * kBWaveLds * sizeof(T);
-  const hipError_t e = ensure_dynamic_lds((const void*)batched_kernel<T>, (int)lds);
-  if (e != hipSuccess) return e;
-  const int grid = (batch + kBWaves - 1) / kBWaves;
-  hipLaunchKernelGGL(batched_kernel<T>, dim3(grid), dim3(256), lds, s, n, batch, A, lda, strideA, ipiv, strideIpiv,
-                     logabs, sign);
-  return hipGetLastError();
+  if (n <= 16) return launch_batched_n<T, 16>(n, batch, A, lda, strideA, ipiv, strideIpiv, logabs, sign, s);
+  if (n <= 32) return launch_batched_n<T, 32>(n, batch, A, lda, strideA, ipiv, strideIpiv, logabs, sign, s);
+  if (n <= 48) return launch_batched_n<T, 48>(n, batch, A, lda, strideA, ipiv, strideIpiv, logabs, sign, s);
+  return launch_batched_n<T, kBMaxN>(n, batch, A, lda, strideA, ipiv, strideIpiv, logabs, sign, s);
 }
 
 template hipError_t launch_batched<double>(int, int, double*, int64_t, int64_t, int*, int64_t, double*, int*,

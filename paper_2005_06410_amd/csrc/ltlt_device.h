@@ -55,53 +55,8 @@ __device__ __forceinline__ void raise_wait_status(int* status) {
   atomicOr(status + 1, 1);
 }
 
-// (|value|, index) pair reduction: larger magnitude wins, ties go to the
-// smaller index.  Magnitudes are compared as doubles (exact for fp32 input).
-__device__ __forceinline__ void argmax_merge(double& bv, int& bi, double ov, int oi) {
-  if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-}
-
-__device__ __forceinline__ void wave_argmax(double& bv, int& bi) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    double ov = __shfl_xor(bv, off, kWave);
-    int oi = __shfl_xor(bi, off, kWave);
-    argmax_merge(bv, bi, ov, oi);
-  }
-}
-
-// One DPP step of a wave-wide (|value|, index) max: every lane merges the
-// pair of the lane selected by CTRL; lanes without a source (row edges,
-// masked rows) merge the identity (-1, INT32_MAX).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_argmax_step(double& v, int& i) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  const int ilo = __double2loint(-1.0), ihi = __double2hiint(-1.0);
-  const int olo = __builtin_amdgcn_update_dpp(ilo, lo, CTRL, ROW_MASK, 0xF, false);
-  const int ohi = __builtin_amdgcn_update_dpp(ihi, hi, CTRL, ROW_MASK, 0xF, false);
-  const int oi = __builtin_amdgcn_update_dpp(INT32_MAX, i, CTRL, ROW_MASK, 0xF, false);
-  const double ov = __hiloint2double(ohi, olo);
-  if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
-}
-
-// Wave-wide argmax through DPP row shifts and row broadcasts (no LDS
-// permutes): the result is complete in lane 63 and returned to all lanes.
-// Values must be >= -1 and not NaN (callers map NaN to -1: not a candidate).
-__device__ __forceinline__ void wave_argmax_dpp(double& v, int& i) {
-  dpp_argmax_step<0x111, 0xF>(v, i);   // row_shr:1
-  dpp_argmax_step<0x112, 0xF>(v, i);   // row_shr:2
-  dpp_argmax_step<0x114, 0xF>(v, i);   // row_shr:4
-  dpp_argmax_step<0x118, 0xF>(v, i);   // row_shr:8   -> lane 15 of each row holds the row's result
-  dpp_argmax_step<0x142, 0xA>(v, i);   // row_bcast:15 into rows 1 and 3
-  dpp_argmax_step<0x143, 0xC>(v, i);   // row_bcast:31 into rows 2 and 3 -> lane 63 complete
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-  v = __hiloint2double(hi, lo);
-  i = __builtin_amdgcn_readlane(i, 63);
-}
-
 // ---------------------------------------------------------------------------
-// Register-resident column refresh and first-maximum search, shared by the
+// Register-resident column refresh and wave-wide maximum, shared by the
 // panel and the batched kernels.
 // ---------------------------------------------------------------------------
 
@@ -166,45 +121,4 @@ __device__ __forceinline__ unsigned wave_umax(unsigned x) {
       : "+v"(x));
   return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
 }
-// First maximum of (value, key) over the wave: the largest value, and among
-// equal values the smallest key (then the lowest lane).  Values are >= 0 for
-// candidates and -1 for lanes without one (NaN is never passed); keys are >= 0
-// (INT32_MAX for no candidate).  The wave maximum is found on the high 32 bits
-// of the value (order-preserving for non-negative doubles, +1 so that 0 means
-// "no candidate").  Lanes that tie there are resolved exactly: when every
-// tied value is +0 -- a stretch of zeros, which zero-structured input gives
-// every wave at every step -- by one more wave reduction of the keys;
-// otherwise (equal high words of nonzero values, rare) one lane at a time.
-// A two-reduction form for every tie was measured slower on dense input: its
-// code changes the schedule of the step loop around it.  Returns the winning
-// lane (-1 when no lane has a candidate) and sets vmax / kmin to its value
-// and key.
-__device__ __forceinline__ int wave_first_max(double v, int key, double& vmax, int& kmin) {
-  const unsigned hk = v >= 0.0 ? (unsigned)__double2hiint(v) + 1u : 0u;
-  const unsigned mh = wave_umax(hk);
-  if (mh == 0) { vmax = -1.0; kmin = INT32_MAX; return -1; }
-  const bool tie_hi = hk == mh;
-  unsigned long long hit = __ballot(tie_hi);
-  int src = __ffsll(hit) - 1;
-  unsigned blo = (unsigned)__builtin_amdgcn_readlane(__double2loint(v), src);
-  kmin = __builtin_amdgcn_readlane(key, src);
-  hit &= hit - 1;
-  if (__builtin_expect(hit != 0, 0)) {
-    if (mh == 1u && __ballot(tie_hi && __double2loint(v) != 0) == 0) {   // every tied value is +0
-      kmin = (int)~wave_umax(tie_hi ? ~(unsigned)key : 0u);
-      src = __ffsll(__ballot(tie_hi && key == kmin)) - 1;
-    } else {
-      while (hit) {
-        const int l2 = __ffsll(hit) - 1;
-        const unsigned lo2 = (unsigned)__builtin_amdgcn_readlane(__double2loint(v), l2);
-        const int k2 = __builtin_amdgcn_readlane(key, l2);
-        if (lo2 > blo || (lo2 == blo && k2 < kmin)) { blo = lo2; kmin = k2; src = l2; }
-        hit &= hit - 1;
-      }
-    }
-  }
-  vmax = __hiloint2double((int)(mh - 1u), (int)blo);
-  return src;
-}
-
 }  // namespace ltlt
