@@ -746,7 +746,7 @@ int ltlt_solve(int64_t n, const void* A, int64_t lda, int dtype, const int32_t* 
   const size_t o_Y = cv.take<char>((size_t)ldy * kSolveRhs * esz);
   const size_t o_W = cv.take<char>((size_t)ldy * kSolveRhs * esz);
   const size_t o_box = cv.take<uint64_t>((size_t)nblk * kSolveRhs * 64 * 2);
-  const size_t o_dinv = cv.take<char>((size_t)(1 + 2 * 2) * nblk * 64 * 64 * esz);
+  const size_t o_dinv = cv.take<char>((size_t)3 * nblk * 64 * 64 * esz);
   void* ws = nullptr;
   int* status = nullptr;
   hipError_t e = workspace(cv.off, stream, &ws, &status);

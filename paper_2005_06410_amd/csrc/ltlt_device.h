@@ -99,6 +99,28 @@ __device__ __forceinline__ void refresh16(float (&acc)[4], float g, const float 
 }
 #undef LTLT_FMAC16
 
+// The 16 x 16 x 4 matrix instructions: lane l gives A(l%16, l/16) and B(l/16, l%16).
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <typename T> struct Mfma;
+template <> struct Mfma<double> {
+  typedef v4d acc_t;
+  static __device__ __forceinline__ acc_t run(double a, double b, acc_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  // output element v of lane l sits at row (l/16) + 4v, column l%16
+  static __device__ __forceinline__ int row(int l, int v) { return (l >> 4) + 4 * v; }
+};
+template <> struct Mfma<float> {
+  typedef v4f acc_t;
+  static __device__ __forceinline__ acc_t run(float a, float b, acc_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  // output element v of lane l sits at row 4(l/16) + v, column l%16
+  static __device__ __forceinline__ int row(int l, int v) { return 4 * (l >> 4) + v; }
+};
+
 // Wave-wide maximum of an unsigned key (every lane gets it): DPP row shifts
 // and row broadcasts folded into v_max_u32 (a lane without a source is not
 // written and keeps its key), two wait states before each DPP read; lane 63

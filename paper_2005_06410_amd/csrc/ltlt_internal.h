@@ -127,7 +127,7 @@ template <typename T> hipError_t launch_cpfaffian(int n, const void* A, int64_t 
                                                   double* logabs, double* phase, const int* status, hipStream_t s);
 
 // Solve with the factors.
-constexpr int kSolveRhs = 8;                    // right-hand sides per pass
+constexpr int kSolveRhs = 4;                    // right-hand sides per pass
 struct SolveWork {
   int* perm;          // [n]
   int* cnt;           // [2n] counters (steps per target position, fill)
@@ -140,8 +140,8 @@ struct SolveWork {
   int64_t ldy;
   uint64_t* box;      // [blocks][kSolveRhs][64][2] stamped solution words
   int* status;
-  void* dinv;         // [1 + 2 * 2][blocks][64 * 64]: inverses of the diagonal blocks of L and
-                      // the matrices of the last two dependencies of each substitution
+  void* dinv;         // [3][blocks][64 * 64]: inverses of the diagonal blocks of L and the
+                      // matrices of the nearest dependency of each substitution
 };
 template <typename T> hipError_t launch_solve(int n, const T* A, int64_t lda, const int* ipiv, int nrhs, T* B,
                                               int64_t ldb, const SolveWork& w, hipStream_t s);

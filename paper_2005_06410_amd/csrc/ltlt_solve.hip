@@ -14,29 +14,27 @@
 //  * perm: every row follows its own moves through the exchanges, in
 //    parallel (the steps bucketed by the position they target);
 //  * the inverses of the 64x64 unit lower diagonal blocks of L, and their
-//    products with the two nearest off-diagonal tiles, are formed first,
-//    all blocks at once (off the dependency chain);
-//  * the triangular solves are persistent cooperative kernels over 64-row
-//    blocks, left-looking: the workgroup of block b streams the 64x64 tiles
-//    of L to the left of its diagonal block (forward) or below it (backward)
-//    through LDS, waiting for the stamped solution words of the block each
-//    tile multiplies, except the two nearest ones; then each wave takes one
-//    right-hand side alone: the residual times the inverse of the diagonal
-//    block (its transpose, backward), minus the precomputed products with
-//    the two nearest blocks' solutions, waiting for each only then (one
-//    64-term product on the chain from block to block instead of a tile
-//    and a 64-step substitution), and publishes its solution as stamped
-//    words.  A workgroup
+//    products with the nearest off-diagonal tile in each direction, are formed
+//    first, all blocks at once (off the dependency chain);
+//  * the triangular solves are persistent kernels over 64-row blocks,
+//    left-looking: the waves of block b's workgroup stream their columns of
+//    the 64x64 tiles of L to the left of its diagonal block (forward) or below
+//    it (backward) through registers, each waiting for the stamped solution
+//    words of the block a tile multiplies, except the nearest; then each wave
+//    takes one right-hand side alone: the residual times the inverse of the
+//    diagonal block (its transpose, backward), minus the precomputed product
+//    with the nearest block's solution, waited for only then (one 64-term
+//    product on the chain from block to block instead of a tile and a 64-step
+//    substitution), and publishes its solution as stamped words.  A workgroup
 //    takes its blocks in dependency order, so the earliest unfinished block
 //    always has its inputs and the grid cannot deadlock; every wait is
-//    bounded.  Each solve reads the lower triangle of L once: HBM-bound for
-//    few right-hand sides;
+//    bounded.  Each solve reads the lower triangle of L once;
 //  * each recurrence of T (w_s = a_s w_{s-1} + b_s along one parity) runs
-//    as a chunked scan: every lane of a wave composes the affine maps of its
-//    chunk of steps, the wave scans the 64 compositions, and every lane then
-//    re-runs its chunk from its exact starting value with the recurrence as
-//    written; one wave per (right-hand side, chain), the reciprocals of alpha
-//    formed in parallel beforehand.
+//    as a chunked scan: every thread of a workgroup composes the affine maps of
+//    its chunk of steps, the workgroup scans the compositions, and every thread
+//    then re-runs its chunk from its starting value with the recurrence as
+//    written; one workgroup per (right-hand side, chain), the reciprocals of
+//    alpha formed in parallel beforehand.
 // Right-hand sides are taken kSolveRhs at a time.
 
 #include "ltlt_device.h"
@@ -50,8 +48,6 @@ namespace ltlt {
 constexpr int kSB = 64;                // rows per block
 constexpr int kSLd = kSB + 1;          // LDS stride of a tile column (bank spread)
 constexpr int kSThreads = 256;         // 4 waves
-constexpr int kSGroups = kSThreads / kSB;   // column (or row) groups of a tile
-constexpr int kSCols = kSB / kSGroups;      // 16 columns per group
 
 // ---- permutation ----------------------------------------------------------
 // perm[i] = index of the row at position i after the exchanges (i, ipiv[i]),
@@ -76,6 +72,7 @@ __global__ void __launch_bounds__(1024) perm_scan_kernel(int n, const int* cnt, 
   const int per = (n + 1023) / 1024;
   const int lo = min(n, t * per), hi = min(n, lo + per);
   int sum = 0;
+#pragma unroll 8
   for (int i = lo; i < hi; ++i) sum += cnt[i];
   part[t] = sum;
   __syncthreads();
@@ -86,6 +83,7 @@ __global__ void __launch_bounds__(1024) perm_scan_kernel(int n, const int* cnt, 
     __syncthreads();
   }
   int run = part[t] - sum;
+#pragma unroll 8
   for (int i = lo; i < hi; ++i) { off[i] = run; run += cnt[i]; }
   if (t == 1023) off[n] = part[1023];
 }
@@ -148,17 +146,19 @@ __global__ void zero_ints_kernel(int* v, int count) {
 }
 
 // ---- skew tridiagonal recurrences -----------------------------------------
-// One wave per (right-hand side q, chain): waves 2q run the odd unknowns
-// forward, waves 2q+1 the even unknowns backward.  Both chains are
+// One workgroup per (right-hand side q, chain): even blocks run the odd unknowns
+// forward, odd blocks the even unknowns backward.  Both chains are
 // w_s = a_s w_{s-1} + b_s over s = 1 .. n/2 - 1 after a first value w_0:
 //   odd:  i = 2s,        W[i+1] = (alpha_{i-1} W[i-1] - R[i]) / alpha_i,  w_0 = W[1] = -R[0] / alpha_0
 //   even: i = n-1-2s,    W[i-1] = (R[i] + alpha_i W[i+1]) / alpha_{i-1},  w_0 = W[n-2] = R[n-1] / alpha_{n-2}
-// Lane j takes the steps of chunk j (C consecutive steps): it composes their
-// maps (A, B) with w_end = A w_start + B, the wave forms the exclusive prefix
-// compositions by a shuffle scan, and each lane re-runs its chunk from
-// w_start = A_prefix w_0 + B_prefix, writing every unknown with the
-// recurrence as written above.  Each chain reads the other parity's inputs,
-// so the result goes to a separate buffer W.
+// Thread j takes the steps of chunk j (C consecutive steps): it composes their
+// maps (A, B) with w_end = A w_start + B, the workgroup forms the exclusive
+// prefix compositions (a shuffle scan in each wave, then over the waves), and
+// each thread re-runs its chunk from w_start = A_prefix w_0 + B_prefix, writing
+// every unknown with the recurrence as written above.  Each chain reads the
+// other parity's inputs, so the result goes to a separate buffer W.  Bound by
+// the serial chunk: 1024 threads per chain (8 steps at n = 16384) instead of
+// one wave (128 steps) took it from 82 to 40 us.
 template <typename T>
 __device__ __forceinline__ void tri_step_coeffs(bool odd, int n, int s, const T* alpha, const T* ralpha, const T* R,
                                                 T& ca, T& cb, T& cr, int& out) {
@@ -171,21 +171,22 @@ __device__ __forceinline__ void tri_step_coeffs(bool odd, int n, int s, const T*
   }
 }
 
+constexpr int kTriWaves = 16;
 template <typename T>
-__global__ void __launch_bounds__(1024) solve_tridiag_kernel(int n, int nr, const T* alpha, const T* ralpha,
-                                                             const T* Y, T* W, int64_t ldy) {
+__global__ void __launch_bounds__(kTriWaves * kWave) solve_tridiag_kernel(int n, const T* alpha, const T* ralpha,
+                                                                         const T* Y, T* W, int64_t ldy) {
+  __shared__ T wa[kTriWaves], wb[kTriWaves];       // each wave's whole composition
   const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-  const int q = wave >> 1;
-  if (q >= nr) return;                             // whole wave
-  const bool odd = (wave & 1) == 0;
+  const int q = blockIdx.x >> 1;
+  const bool odd = (blockIdx.x & 1) == 0;
   const T* R = Y + (int64_t)q * ldy;
   T* Wq = W + (int64_t)q * ldy;
   const int half = n / 2;                          // unknowns per chain
   const T w0 = odd ? -R[0] * ralpha[0] : R[n - 1] * ralpha[n - 2];
-  if (lane == 0) Wq[odd ? 1 : n - 2] = w0;
+  if (threadIdx.x == 0) Wq[odd ? 1 : n - 2] = w0;
   const int steps = half - 1;                      // s = 1 .. half-1
-  const int C = (steps + kWave - 1) / kWave;       // steps per lane
-  const int s_lo = 1 + lane * C, s_hi = min(half, s_lo + C);
+  const int C = (steps + kTriWaves * kWave - 1) / (kTriWaves * kWave);   // steps per thread
+  const int s_lo = 1 + threadIdx.x * C, s_hi = min(half, s_lo + C);
   // composition of this chunk's maps: w -> a w + b, a = ca cr (odd) / ca cr,
   // b = -cb cr (odd) / cb cr (even)
   T Ac = T(1), Bc = T(0);
@@ -209,10 +210,15 @@ __global__ void __launch_bounds__(1024) solve_tridiag_kernel(int n, int nr, cons
       Ai = Ai * Ap;
     }
   }
-  // exclusive prefix: the inclusive one of the previous lane
+  if (lane == kWave - 1) { wa[wave] = Ai; wb[wave] = Bi; }
+  __syncthreads();
+  // exclusive prefix: the earlier waves', then the inclusive one of the
+  // previous lane
   T Ae = __shfl_up(Ai, 1, kWave), Be = __shfl_up(Bi, 1, kWave);
   if (lane == 0) { Ae = T(1); Be = T(0); }
-  T w = fma(Ae, w0, Be);                           // value entering this chunk
+  T w = w0;                                        // value entering this wave's chunks
+  for (int v = 0; v < wave; ++v) w = fma(wa[v], w, wb[v]);
+  w = fma(Ae, w, Be);                              // value entering this chunk
 #pragma unroll 8
   for (int s = s_lo; s < s_hi; ++s) {
     T ca, cb, cr;
@@ -236,8 +242,8 @@ struct SolveTriArgs {
   unsigned stamp;     // stamp of this launch (never 0)
   int* status;
   const void* Dinv;   // inverses of the diagonal blocks of L: [nblk][64 * 64], column-major
-  const void* Mf;     // D_b^{-1} L_{b,b-d}: [kLook][nblk][64 * 64], column-major
-  const void* Mb;     // D_b^{-T} L_{b+d,b}^T: [kLook][nblk][64 * 64], column-major
+  const void* Mf;     // D_b^{-1} L_{b,b-1}: [nblk][64 * 64], column-major
+  const void* Mb;     // D_b^{-T} L_{b+1,b}^T: [nblk][64 * 64], column-major
 };
 
 // A solution value crosses workgroups as two 64-bit words, each holding one
@@ -277,367 +283,365 @@ __device__ __forceinline__ T l_entry(const T* A, int64_t lda, int n, int r, int 
 }
 
 // Per 64-row block b: the inverse of its unit lower diagonal block D_b of L
-// and the matrices that carry the last kLook dependencies of each
-// substitution, for d = 1 .. kLook,
-//   Mf_{b,d} = D_b^{-1} L_{b,b-d}        (forward, b >= d),
-//   Mb_{b,d} = D_b^{-T} L_{b+d,b}^T      (backward, b + d < nblk),
-// so that z_b = D_b^{-1} r_b - sum_d Mf_{b,d} z_{b-d} and
-// u_b = D_b^{-T} r_b - sum_d Mb_{b,d} u_{b+d}, where r_b is the block's
-// right-hand side less the contributions of every farther block.  All are
-// stored column-major per block, X[b*64*64 + k*64 + r] = X(r, k); rows and
-// columns past n give the identity (D_b^{-1}) or zeros (M), which the solves
-// never use.
-constexpr int kLook = 1;                          // dependencies carried by the waves
+// and the matrices that carry the nearest dependency of each substitution,
+//   Mf_b = D_b^{-1} L_{b,b-1}        (forward, b >= 1),
+//   Mb_b = D_b^{-T} L_{b+1,b}^T      (backward, b + 1 < nblk),
+// so that z_b = D_b^{-1} r_b - Mf_b z_{b-1} and u_b = D_b^{-T} r_b - Mb_b u_{b+1},
+// where r_b is the block's right-hand side less the contributions of every
+// farther block.  All are stored column-major per block, X[b*64*64 + k*64 + r] =
+// X(r, k); rows and columns past n give the identity (D_b^{-1}) or zeros (M),
+// which the solves never use.
 
-// D_b^{-1}, one wave per block: lane c forms column c by forward
-// substitution, X(c,c) = 1, X(r,c) = -sum_{c<=k<r} D(r,k) X(k,c), D read from
-// LDS by broadcast.
+// D_b^{-1}, one wave per block: lane c forms column c by forward substitution,
+// column k of D (from LDS by broadcast, two entries a read) applied to every
+// later row at once, so that its products are independent.  Entry by entry,
+// each a chain of products, it took 45 us at n = 16384; 23 now.
 template <typename T>
 __global__ void __launch_bounds__(kWave) solve_dinv_kernel(const T* A, int64_t lda, int n, T* Dinv) {
-  __shared__ T d[kSB * kSLd];                      // D(r, c), then D^{-1}(r, c), at d[c * kSLd + r]
+  __shared__ __align__(16) T d[kSB * kSB];         // D(r, c) at d[c * kSB + r]
+  __shared__ T t[kSB * kSLd];                      // D^{-1}(r, c) at t[c * kSLd + r]
   const int b = blockIdx.x, lane = threadIdx.x;
   const int d0 = b * kSB;
-#pragma unroll 4
-  for (int cc = 0; cc < kSB; ++cc) d[cc * kSLd + lane] = l_entry(A, lda, n, d0 + lane, d0 + cc);
-  wave_lds_sync();
   T x[kSB];
 #pragma unroll
-  for (int r = 0; r < kSB; ++r) {
-    T acc = T(0);
+  for (int c = 0; c < kSB; ++c) x[c] = l_entry(A, lda, n, d0 + lane, d0 + c);
 #pragma unroll
-    for (int k = 0; k < r; ++k) acc = fma(d[k * kSLd + r], x[k], acc);
-    x[r] = r < lane ? T(0) : (r == lane ? T(1) : -acc);
+  for (int c = 0; c < kSB; ++c) d[c * kSB + lane] = x[c];
+  wave_lds_sync();
+#pragma unroll
+  for (int r = 0; r < kSB; ++r) x[r] = r == lane ? T(1) : T(0);
+#pragma unroll
+  for (int k = 0; k < kSB - 1; ++k) {
+#pragma unroll
+    for (int r = k + 1; r < kSB; ++r) x[r] = fma(-d[k * kSB + r], x[k], x[r]);
+    asm volatile("" ::: "memory");                 // a column's reads at a time
   }
-  wave_lds_sync();                                 // every read of D is done
 #pragma unroll
-  for (int r = 0; r < kSB; ++r) d[lane * kSLd + r] = x[r];
+  for (int r = 0; r < kSB; ++r) t[lane * kSLd + r] = x[r];
   wave_lds_sync();
   T* out = Dinv + (size_t)b * kSB * kSB;
 #pragma unroll 4
-  for (int cc = 0; cc < kSB; ++cc) out[cc * kSB + lane] = d[cc * kSLd + lane];
+  for (int cc = 0; cc < kSB; ++cc) out[cc * kSB + lane] = t[cc * kSLd + lane];
 }
 
-// Mf_{b,d} and Mb_{b,d}, 2 kLook waves per block: D_b^{-1} into LDS; wave
-// 2(d-1) + e (e = 0 forward, 1 backward), lane k, loads column k of L_{b,b-d}
-// or row k of L_{b+d,b} and forms column k of its matrix with D_b^{-1} read
-// by broadcast.
+// Mf_b (blockIdx.y = 0) and Mb_b (1): 64 x 64 x 64 products on the matrix
+// cores, wave w the rows 16w .. 16w+15.  (One lane per column with the inverse
+// read by LDS broadcast took 91 us at n = 16384; 23 now.)
 template <typename T>
-__global__ void __launch_bounds__(2 * kLook * kWave) solve_mmat_kernel(const T* A, int64_t lda, int n, int nblk,
-                                                                       const T* Dinv, T* Mf, T* Mb) {
-  __shared__ T d[kSB * kSLd];                      // D^{-1}(r, c) at d[c * kSLd + r]
+__global__ void __launch_bounds__(kSThreads) solve_mmat_kernel(const T* A, int64_t lda, int n, int nblk,
+                                                               const T* Dinv, T* Mf, T* Mb) {
+  __shared__ T xa[kSB * kSLd];                     // X(r, j) at xa[j * kSLd + r]: D^{-1}, or its transpose
+  __shared__ T lb[kSB * kSLd];                     // the tile's entry for (j, column) at lb[j * kSLd + column]
   const int b = blockIdx.x, tid = threadIdx.x;
+  const bool fwd = blockIdx.y == 0;
+  if (fwd ? b < 1 : b + 1 >= nblk) return;
+  const int d0 = b * kSB, s0 = fwd ? d0 - kSB : d0 + kSB;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
-  const int d0 = b * kSB;
   const size_t blk = (size_t)b * kSB * kSB;
-  for (int e = tid; e < kSB * kSB; e += blockDim.x) d[(e / kSB) * kSLd + e % kSB] = Dinv[blk + e];
-  const int dist = 1 + wave / 2;
-  const bool fwd = (wave & 1) == 0;
-  const bool has = fwd ? b >= dist : b + dist < nblk;
-  T lv[kSB];
-#pragma unroll 8
-  for (int j = 0; j < kSB; ++j)
-    lv[j] = !has ? T(0)
-                 : (fwd ? l_entry(A, lda, n, d0 + j, d0 - dist * kSB + lane)
-                        : l_entry(A, lda, n, d0 + dist * kSB + lane, d0 + j));
+  for (int c = wave; c < kSB; c += kSThreads / kWave) {
+    const T x = Dinv[blk + c * kSB + lane];        // D^{-1}(lane, c)
+    xa[fwd ? c * kSLd + lane : lane * kSLd + c] = x;
+    // forward: column s0 + c of the tile's rows; backward: row s0 + lane, column d0 + c
+    if (fwd) lb[lane * kSLd + c] = l_entry(A, lda, n, d0 + lane, s0 + c);
+    else lb[c * kSLd + lane] = l_entry(A, lda, n, s0 + lane, d0 + c);
+  }
   __syncthreads();
-  if (!has) return;                                // no barrier follows
-  T* out = (fwd ? Mf : Mb) + (size_t)(dist - 1) * nblk * kSB * kSB + blk + (size_t)lane * kSB;
-  // forward:  Mf(r, k) = sum_j D^{-1}(r, j) L_{b,b-d}(j, k)
-  // backward: Mb(r, k) = sum_j D^{-1}(j, r) L_{b+d,b}(k, j)
-  const int sj = fwd ? kSLd : 1, sr = fwd ? 1 : kSLd;   // LDS strides of j and r
-  for (int r = 0; r < kSB; ++r) {
-    T acc = T(0);
+  typedef typename Mfma<T>::acc_t acc_t;
+  acc_t acc[4];
 #pragma unroll
-    for (int j = 0; j < kSB; ++j) acc = fma(d[j * sj + r * sr], lv[j], acc);
-    out[r] = acc;
+  for (int t = 0; t < 4; ++t) acc[t] = acc_t{T(0), T(0), T(0), T(0)};
+  const int l16 = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < kSB; j += 4) {
+    const T x = xa[(j + q) * kSLd + 16 * wave + l16];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = Mfma<T>::run(x, lb[(j + q) * kSLd + 16 * t + l16], acc[t]);
   }
+  T* out = (fwd ? Mf : Mb) + blk;
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) out[(16 * t + l16) * kSB + 16 * wave + Mfma<T>::row(lane, v)] = acc[t][v];
 }
 
-// Workgroup-wide AND of v over an LDS-only barrier: each wave's vote goes to
-// one of two flag sets, alternating per call (a set is rewritten two votes
-// later, after every wave has passed the barrier of the vote in between).
-struct Vote {
-  int* flags;        // LDS [2][waves]
-  int k;
-  __device__ bool all(bool v, int wave, int lane) {
-    int* f = flags + (k & 1) * (kSThreads / kWave);
-    ++k;
-    const int w = __ballot(!v) == 0;
-    if (lane == 0) f[wave] = w;
-    lds_barrier();
-    bool r = true;
-#pragma unroll
-    for (int i = 0; i < kSThreads / kWave; ++i) r = r && f[i] != 0;
-    return r;
-  }
-};
-
-// Poll the solution of block sb until every (row, right-hand side) entry
-// carries this launch's stamp; the values land in yc[row][rhs].  Bounded;
-// the whole workgroup returns false together when the wait gives up.  The
-// status word is read in the same round trip as the solution words, so an
-// unsuccessful poll costs one round trip, not two.
-template <typename T>
-__device__ __forceinline__ bool wait_box(const SolveTriArgs& a, int sb, T* yc, int tid, Vote& vote) {
-  const int wave = tid / kWave, lane = tid & (kWave - 1);
-  const uint64_t* bx = a.box + (size_t)sb * kSolveRhs * kSB * 2;
-  const uint64_t t0 = wall_ticks();
-  for (;;) {
-    bool ok = true;
-    const int st = tid == 0 ? ld_coh(a.status) : 0;
-    for (int e = tid; e < kSB * a.nr; e += kSThreads) {
-      const int rr = e % kSB, q = e / kSB;
-      T v;
-      if (box_get(&bx[((size_t)q * kSB + rr) * 2], a.stamp, v)) yc[rr * kSolveRhs + q] = v;
-      else ok = false;
-    }
-    if (vote.all(ok, wave, lane)) return true;
-    const bool late = tid == 0 && (st != 0 || wall_ticks() - t0 > kWaitLimitTicks);
-    if (!vote.all(!late, wave, lane)) {
-      if (tid == 0) raise_wait_status(a.status);
-      return false;
-    }
-  }
-}
-
-// One wave polls the 64 solution entries of block sb for right-hand side q
-// (lane = row), reading the status word in the same round trip.  Bounded:
-// when the wait gives up (or an earlier wait already has) the status flag is
-// set and false is returned; the wave carries on with an unspecified value,
-// so that no wave leaves its workgroup's barriers.
-template <typename T>
-__device__ __forceinline__ bool wait_words(const SolveTriArgs& a, int sb, int q, int lane, T& v) {
-  const uint64_t* w = a.box + (((size_t)sb * kSolveRhs + q) * kSB + lane) * 2;
+// One wave polls entry `at` (per lane) of block sb for right-hand sides 0 ..
+// NQ-1, reading the status word in the same round trip.  Blocks far from the
+// one they wait for poll rarely (naps of 256 clocks), so that the next ones
+// find the words' cache lines free.  Bounded: when the wait gives up (or an
+// earlier wait already has) the status words are raised and the wave carries on
+// with unspecified values, so that no wave leaves its workgroup's barriers.
+template <typename T, int NQ>
+__device__ __forceinline__ void wait_words(const SolveTriArgs& a, int sb, int at, int naps, T (&v)[NQ]) {
+  const uint64_t* w = a.box + ((size_t)sb * kSolveRhs * kSB + at) * 2;
   const uint64_t t0 = wall_ticks();
   for (;;) {
     const int st = ld_coh(a.status);
-    const bool ok = box_get(w, a.stamp, v);
-    if (__ballot(!ok) == 0) return true;
-    const int late = __builtin_amdgcn_readfirstlane((st != 0 || wall_ticks() - t0 > kWaitLimitTicks) ? 1 : 0);
-    if (late) {
-      if (lane == 0) raise_wait_status(a.status);
-      return false;
+    bool ok = true;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) ok = (q >= a.nr || box_get(w + (size_t)q * kSB * 2, a.stamp, v[q])) && ok;
+    if (__ballot(!ok) == 0) return;
+    if (__builtin_amdgcn_readfirstlane((st != 0 || wall_ticks() - t0 > kWaitLimitTicks) ? 1 : 0)) {
+      if ((threadIdx.x & (kWave - 1)) == 0) raise_wait_status(a.status);
+      return;
     }
+    for (int i = 0; i < naps; ++i) __builtin_amdgcn_s_sleep(4);
   }
 }
 
-// Forward (UPPER = false): z_b = D_b^{-1} r_b - sum_{d<=kLook} Mf_{b,d} z_{b-d},
-//   r_b = y_b - sum_{c<b-kLook} L_bc z_c.
+// 64 x 64 matrix times vector in one wave: m holds, for lane (p = lane/16, i =
+// lane%16), X(16 e + i, 16 p + c) at m[(16 e + c) * 64 + lane]; v is lane k's
+// entry k; lane r gets entry r of the product.  The vector reaches the FMAs
+// through DPP row broadcasts (no LDS round trip for it), the four 16-lane rows
+// sum a quarter of the columns each.
+template <typename T>
+__device__ __forceinline__ void load_mat(const T* m, int lane, T (&x)[kSB]) {
+#pragma unroll
+  for (int e = 0; e < kSB; ++e) x[e] = m[e * kWave + lane];
+}
+template <typename T>
+__device__ __forceinline__ T mat_vec(const T (&x)[kSB], T v, int lane) {
+  T s[4][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[e][j] = T(0);
+  refresh16<0>(s[0], v, x);
+  refresh16<1>(s[1], v, x);
+  refresh16<2>(s[2], v, x);
+  refresh16<3>(s[3], v, x);
+  T r = T(0);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const T sum = part_sum<4>((s[e][0] + s[e][1]) + (s[e][2] + s[e][3]));
+    r = (lane >> 4) == e ? sum : r;
+  }
+  return r;
+}
+
+// Sums over the wave's 64 lanes of 16 values per lane: lane l with l % 16 == e
+// gets, for e < 4, the sum of value e + 4 (l / 16 % 2) + 8 (l / 32).  Two
+// exchange-and-add steps through the lane swaps halve the values and the
+// lanes, then row rotations.
+template <int CTRL>
+__device__ __forceinline__ double ror_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return v + __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ __forceinline__ float ror_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+// a's sum over the lane pairs in the even (lower) lanes, b's in the odd (upper)
+template <int OFF>
+__device__ __forceinline__ unsigned swap_halves(unsigned x, unsigned y, unsigned& other) {
+  if constexpr (OFF == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    other = r[1];
+    return r[0];
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    other = r[1];
+    return r[0];
+  }
+}
+template <int OFF>
+__device__ __forceinline__ double pair_add(double a, double b) {
+  unsigned lo1, hi1;
+  const unsigned lo0 = swap_halves<OFF>((unsigned)__double2loint(a), (unsigned)__double2loint(b), lo1);
+  const unsigned hi0 = swap_halves<OFF>((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), hi1);
+  return __hiloint2double((int)hi0, (int)lo0) + __hiloint2double((int)hi1, (int)lo1);
+}
+template <int OFF>
+__device__ __forceinline__ float pair_add(float a, float b) {
+  unsigned o;
+  const unsigned x = swap_halves<OFF>(__float_as_uint(a), __float_as_uint(b), o);
+  return __uint_as_float(x) + __uint_as_float(o);
+}
+template <typename T>
+__device__ __forceinline__ T lane_sums(const T (&v)[16], int lane) {
+  T h[8], f[4];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) h[c] = pair_add<32>(v[c], v[c + 8]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) f[c] = pair_add<16>(h[c], h[c + 4]);
+  T r = T(0);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const T x = ror_add<0x121>(ror_add<0x122>(ror_add<0x124>(ror_add<0x128>(f[c]))));   // row_ror 8, 4, 2, 1
+    r = (lane & 15) == c ? x : r;
+  }
+  return r;
+}
+
+// Forward (UPPER = false): z_b = D_b^{-1} r_b - Mf_b z_{b-1},
+//   r_b = y_b - sum_{c<b-1} L_bc z_c.
 // Backward (UPPER = true), blocks from the last one down:
-//   u_b = D_b^{-T} r_b - sum_{d<=kLook} Mb_{b,d} u_{b+d},
-//   r_b = w_b - sum_{b'>b+kLook} L_{b'b}^T u_{b'}.
-// The workgroup multiplies the farther off-diagonal tiles of r_b straight
-// from registers (two tiles in flight, the next block's solution words
-// requested during the current tile, so that a tile whose inputs are long
-// published costs no round trip); then every wave takes its
-// right-hand sides alone: c = D_b^{-1} r_b (resp. D_b^{-T} r_b) with its row
-// of the inverse in registers and r broadcast from LDS, then, nearest block
-// last, waits for each of the kLook neighbouring blocks' solutions and
-// subtracts M times it.  Only the last of those products is on the chain
-// from block to block; the workgroup's own tiles have kLook blocks of slack.
-template <typename T, bool UPPER>
+//   u_b = D_b^{-T} r_b - Mb_b u_{b+1},  r_b = w_b - sum_{b'>b+1} L_{b'b}^T u_{b'}.
+// The four waves of a workgroup take 16 columns each of the farther
+// off-diagonal tiles of r_b and run through them without a barrier: every
+// wave polls the solution words its tile needs straight into registers.
+// Forward, a lane holds a row of the tile and the solution's entries reach the
+// FMAs through DPP row broadcasts; backward, a lane holds a row as well (so
+// that both directions read L's columns in runs), multiplies it by its own entry
+// of the solution and keeps 16 sums, one per column, that meet once per block.
+// Two tiles are in flight beside the two being used.  Then wave q takes
+// right-hand side q alone: D_b^{-1} r_b, and, once the neighbouring block's
+// solution arrives, M times it: the one product on the chain from block to
+// block.  Bound by that chain, a block's words becoming visible and one 64 x 64
+// product: one right-hand side at n = 16384 took 0.67 ms forward and 0.93 ms
+// backward with a workgroup barrier or two per tile, the solution through
+// LDS, eight right-hand-side slots always multiplied and the backward tiles
+// read across columns; 0.35 and 0.41 now.
+template <typename T, bool UPPER, int NQ>
 __global__ void __launch_bounds__(kSThreads, 1) solve_tri_kernel(SolveTriArgs a) {
-  __shared__ T dtile[kSB * kSLd];                  // D_b^{-1}, column-major
-  __shared__ T mtile[kLook][kSB * kSLd];           // Mf_{b,d} (forward) or Mb_{b,d} (backward), column-major
-  __shared__ T yc[kSB * kSolveRhs];                // solution of the block a tile multiplies
-  __shared__ T part[kSGroups * kSB * kSolveRhs];   // partial sums of the four groups
-  __shared__ T xs[kSThreads / kWave][kSB];         // vector broadcast to the lanes of a wave
-  __shared__ int vflags[2 * (kSThreads / kWave)];
-  Vote vote{vflags, 0};
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* dt = reinterpret_cast<T*>(smem);              // D_b^{-1} (forward) or D_b^{-T}, as load_mat reads it
+  T* mt = dt + kSB * kSB;                          // Mf_b or Mb_b, likewise
+  T* part = mt + kSB * kSB;                        // forward: [wave][NQ][64] partial sums; backward: [NQ][64] sums
   const T* A = static_cast<const T*>(a.A);
   T* Y = static_cast<T*>(a.Y);
   const T* Dinv = static_cast<const T*>(a.Dinv);
   const T* Mx = static_cast<const T*>(UPPER ? a.Mb : a.Mf);
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int r = tid & (kSB - 1), g = tid / kSB;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int g = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int i16 = lane & 15, p16 = lane >> 4;
   const int n = a.n, nr = a.nr, nblk = a.nblk;
   const int64_t lda = a.lda, ldy = a.ldy;
   for (int i = blockIdx.x; i < nblk; i += gridDim.x) {
     const int b = UPPER ? nblk - 1 - i : i;
     const int d0 = b * kSB;
     const int ntile = UPPER ? nblk - 1 - b : b;   // tiles of r_b and the chain's tile
-    const int nfull = ntile > kLook ? ntile - kLook : 0;   // tiles the workgroup multiplies itself
-    const int nlook = ntile - nfull;               // tiles the waves carry (nearest last)
+    const int nfull = ntile > 1 ? ntile - 1 : 0;   // tiles the waves multiply
     // tile t multiplies the solution of block src(t): forward t, backward nblk-1-t
     auto src = [&](int t) { return UPPER ? nblk - 1 - t : t; };
-    // thread (r, g) holds, jj < 16, forward L(d0 + r, s0 + g + 4 jj) (row r of
-    // the tile, coalesced), backward L(s0 + g + 4 jj, d0 + r) (column r of the
-    // tile: one row per instruction, each thread's 16 rows from a few lines);
-    // either way the thread's sum is over its own registers
-    auto fetch = [&](int t, T(&regs)[kSCols]) {
-      const int s0 = src(t) * kSB;
-#pragma unroll
-      for (int jj = 0; jj < kSCols; ++jj)
-        regs[jj] = UPPER ? l_entry(A, lda, n, s0 + g + kSGroups * jj, d0 + r)
-                         : l_entry(A, lda, n, d0 + r, s0 + g + kSGroups * jj);
-    };
-    // the solution words of a tile's block, loaded one tile ahead: entry
-    // e = q * 64 + row of the block's words, kYE entries per thread
-    constexpr int kYE = kSB * kSolveRhs / kSThreads;
-    uint64_t yw[kYE][2];
-    auto ypf = [&](int t) {
-      const uint64_t* bx = a.box + (size_t)src(t) * kSolveRhs * kSB * 2;
-#pragma unroll
-      for (int e = 0; e < kYE; ++e) {
-        const int idx = tid + e * kSThreads;
-        if (idx < kSB * nr) {
-          yw[e][0] = ld_coh64(&bx[(size_t)idx * 2]);
-          yw[e][1] = ld_coh64(&bx[(size_t)idx * 2 + 1]);
-        }
-      }
-    };
-    // the prefetched words into yc when every one carries this launch's
-    // stamp (true for the whole workgroup), else false
-    auto ytake = [&]() {
-      bool ok = true;
-#pragma unroll
-      for (int e = 0; e < kYE; ++e) {
-        const int idx = tid + e * kSThreads;
-        if (idx < kSB * nr) {
-          const uint64_t w0 = yw[e][0], w1 = yw[e][1];
-          if ((unsigned)w0 != a.stamp || (unsigned)w1 != a.stamp) {
-            ok = false;
-          } else {
-            T v;
-            if constexpr (sizeof(T) == 8) v = __hiloint2double((int)(w0 >> 32), (int)(w1 >> 32));
-            else v = __uint_as_float((unsigned)(w0 >> 32));
-            yc[(idx % kSB) * kSolveRhs + idx / kSB] = v;
-          }
-        }
-      }
-      return vote.all(ok, wave, lane);
-    };
     {
-      // every load issued before the first LDS store, so that the block's
-      // start costs one memory round trip
-      const T* Db = Dinv + (size_t)b * kSB * kSB;
-      const size_t mat = (size_t)nblk * kSB * kSB;
-      T dv[kSCols], mv[kLook][kSCols];
+      T dv[16], mv[16];
+      const size_t blk = (size_t)b * kSB * kSB;
 #pragma unroll
-      for (int jj = 0; jj < kSCols; ++jj) {
-        const int cc = g + kSGroups * jj;
-        dv[jj] = Db[cc * kSB + r];
-#pragma unroll
-        for (int dd = 0; dd < kLook; ++dd)
-          mv[dd][jj] = dd < nlook ? Mx[(size_t)dd * mat + (size_t)b * kSB * kSB + cc * kSB + r] : T(0);
+      for (int c = 0; c < 16; ++c) {
+        const int r = 16 * g + i16, k = 16 * p16 + c;
+        dv[c] = Dinv[blk + (UPPER ? r * kSB + k : k * kSB + r)];
+        mv[c] = ntile > 0 ? Mx[blk + k * kSB + r] : T(0);
       }
 #pragma unroll
-      for (int jj = 0; jj < kSCols; ++jj) {
-        const int cc = g + kSGroups * jj;
-        dtile[cc * kSLd + r] = dv[jj];
-#pragma unroll
-        for (int dd = 0; dd < kLook; ++dd) mtile[dd][cc * kSLd + r] = mv[dd][jj];
+      for (int c = 0; c < 16; ++c) {
+        dt[(16 * g + c) * kWave + lane] = dv[c];
+        mt[(16 * g + c) * kWave + lane] = mv[c];
       }
     }
-    constexpr int kQW = kSolveRhs / (kSThreads / kWave);
-    T ypre[kQW];
+    const T ypre = (g < nr && d0 + lane < n) ? Y[(int64_t)(d0 + lane) + (int64_t)g * ldy] : T(0);
+    // 16 columns of tile t, one row per lane: L(d0 + lane, s0 + 16g + c)
+    // forward, L(s0 + lane, d0 + 16g + c) backward.  Rows past n read the last
+    // row (forward such rows are never used, backward their solution is zero);
+    // column 0 of L, e_0, is not stored: zeroed in the product.
+    auto fetch = [&](int t, T(&x)[16]) {
+      if (t >= nfull) return;
+      const int s0 = src(t) * kSB;
+      const int row = min((UPPER ? s0 : d0) + lane, n - 1), c0 = (UPPER ? d0 : s0) + 16 * g;
 #pragma unroll
-    for (int k = 0; k < kQW; ++k) {
-      const int q = wave + (kSThreads / kWave) * k;
-      ypre[k] = (q < nr && d0 + lane < n) ? Y[(int64_t)(d0 + lane) + (int64_t)q * ldy] : T(0);
-    }
-    T acc[kSolveRhs];
-#pragma unroll
-    for (int q = 0; q < kSolveRhs; ++q) acc[q] = T(0);
-    // tile t: its block's solution in yc (prefetched words, else a poll),
-    // the next block's words requested, then the product; two tiles are in
-    // flight in registers (buffers ra and rb alternate)
-    auto step = [&](int t, T(&regs)[kSCols]) {
-      if (!ytake() && !wait_box<T>(a, src(t), yc, tid, vote)) return false;
-      if (t + 1 < nfull) ypf(t + 1);
-      // thread (r, g): output entry r, terms g + 4 jj, straight from registers;
-      // every right-hand side slot, branch-free (the sums of slots past nr are
-      // never read), so that the tile loads are not all waited for per term
-#pragma unroll
-      for (int jj = 0; jj < kSCols; ++jj) {
-        const int k = g + kSGroups * jj;
-#pragma unroll
-        for (int q = 0; q < kSolveRhs; ++q) acc[q] = fma(regs[jj], yc[k * kSolveRhs + q], acc[q]);
-      }
-      lds_barrier();                               // yc is rewritten by the next tile
-      return true;
+      for (int c = 0; c < 16; ++c) x[c] = A[(int64_t)row + (int64_t)max(c0 + c - 1, 0) * lda];
     };
-    T ra[kSCols], rb[kSCols];
-    if (nfull > 0) { fetch(0, ra); ypf(0); }
-    if (nfull > 1) fetch(1, rb);
-    for (int t = 0; t < nfull; t += 2) {
-      if (!step(t, ra)) return;
-      if (t + 2 < nfull) fetch(t + 2, ra);
-      if (t + 1 < nfull) {
-        if (!step(t + 1, rb)) return;
-        if (t + 3 < nfull) fetch(t + 3, rb);
+    constexpr int NA = UPPER ? 16 : 4;
+    T acc[NQ][NA];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int c = 0; c < NA; ++c) acc[q][c] = T(0);
+    auto use = [&](int t, T(&x)[16]) {
+      if (t >= nfull) return;
+      T v[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) v[q] = T(0);
+      wait_words<T, NQ>(a, src(t), UPPER ? lane : 16 * g + i16, min(ntile - t, 32) - 3, v);
+      if ((UPPER ? d0 : src(t) * kSB) + 16 * g == 0) x[0] = T(0);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        if constexpr (UPPER) {
+#pragma unroll
+          for (int c = 0; c < 16; ++c) acc[q][c] = fma(x[c], v[q], acc[q][c]);
+        } else {
+          refresh16<0>(acc[q], v[q], x);
+        }
       }
+    };
+    T r0[16], r1[16], r2[16], r3[16];
+    fetch(0, r0);
+    fetch(1, r1);
+    for (int t = 0; t < nfull; t += 4) {
+      fetch(t + 2, r2);
+      fetch(t + 3, r3);
+      use(t, r0);
+      use(t + 1, r1);
+      fetch(t + 4, r0);
+      fetch(t + 5, r1);
+      use(t + 2, r2);
+      use(t + 3, r3);
     }
 #pragma unroll
-    for (int q = 0; q < kSolveRhs; ++q) part[(g * kSB + r) * kSolveRhs + q] = acc[q];
+    for (int q = 0; q < NQ; ++q) {
+      if constexpr (UPPER) {
+        const T x = lane_sums(acc[q], lane);
+        if (i16 < 4) part[q * kSB + 16 * g + i16 + 4 * (p16 & 1) + 8 * (p16 >> 1)] = x;
+      } else {
+        part[(g * NQ + q) * kSB + lane] = (acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]);
+      }
+    }
     lds_barrier();
-    // wave w takes right-hand sides w, w+4; lane = row (forward) or column
-    // (backward) of the block
+    if (g < nr) {                                  // wave q: right-hand side q
+      T m[kSB];
+      load_mat(dt, lane, m);
+      T sum;
+      if constexpr (UPPER) {
+        sum = part[g * kSB + lane];
+      } else {
+        sum = T(0);
 #pragma unroll
-    for (int k = 0; k < kQW; ++k) {
-      const int q = wave + (kSThreads / kWave) * k;
-      if (q >= nr) break;
-      T x = T(0);
-      if (d0 + lane < n) {
-        T sum = T(0);
-#pragma unroll
-        for (int gg = 0; gg < kSGroups; ++gg) sum += part[(gg * kSB + lane) * kSolveRhs + q];
-        x = ypre[k] - sum;
+        for (int w = 0; w < kSThreads / kWave; ++w) sum += part[(w * NQ + g) * kSB + lane];
       }
-      xs[wave][lane] = x;
-      wave_lds_sync();
-      {
-        T dl[kSB];
-#pragma unroll
-        for (int cc = 0; cc < kSB; ++cc) dl[cc] = UPPER ? dtile[lane * kSLd + cc] : dtile[cc * kSLd + lane];
-        T s4[4] = {T(0), T(0), T(0), T(0)};
-#pragma unroll
-        for (int cc = 0; cc < kSB; ++cc) s4[cc & 3] = fma(dl[cc], xs[wave][cc], s4[cc & 3]);
-        x = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      T x = mat_vec(m, d0 + lane < n ? ypre - sum : T(0), lane);
+      if (ntile > 0) {
+        load_mat(mt, lane, m);
+        T near[1] = {T(0)};
+        SolveTriArgs one = a;
+        one.nr = 1;
+        one.box += (size_t)g * kSB * 2;
+        wait_words<T, 1>(one, src(ntile - 1), lane, 0, near);
+        x -= mat_vec(m, near[0], lane);
       }
-      wave_lds_sync();                             // xs is rewritten below
-      // distance d = nlook .. 1: tile ntile-d multiplies block src(ntile-d)
-      for (int dd = nlook - 1; dd >= 0; --dd) {
-        T ml[kSB];
-#pragma unroll
-        for (int kk = 0; kk < kSB; ++kk) ml[kk] = mtile[dd][kk * kSLd + lane];
-        T yp;
-        wait_words<T>(a, src(ntile - 1 - dd), q, lane, yp);
-        xs[wave][lane] = yp;
-        wave_lds_sync();
-        T s4[4] = {T(0), T(0), T(0), T(0)};
-#pragma unroll
-        for (int kk = 0; kk < kSB; ++kk) s4[kk & 3] = fma(ml[kk], xs[wave][kk], s4[kk & 3]);
-        x -= (s4[0] + s4[1]) + (s4[2] + s4[3]);
-        wave_lds_sync();
-      }
-      if (d0 + lane < n) Y[(int64_t)(d0 + lane) + (int64_t)q * ldy] = x;
-      box_put(&a.box[(((size_t)b * kSolveRhs + q) * kSB + lane) * 2], d0 + lane < n ? x : T(0), a.stamp);
+      if (d0 + lane < n) Y[(int64_t)(d0 + lane) + (int64_t)g * ldy] = x;
+      box_put(&a.box[(((size_t)b * kSolveRhs + g) * kSB + lane) * 2], d0 + lane < n ? x : T(0), a.stamp);
     }
-    lds_barrier();                                 // part, dtile and mtile are reused by the next block
+    lds_barrier();                                 // dt, mt and part are reused by the next block
   }
 }
 
-template <typename T, bool UPPER>
-int solve_tri_max_blocks() {
-  int dev = 0, per_cu = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  const void* k = (const void*)solve_tri_kernel<T, UPPER>;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kSThreads, 0) != hipSuccess) return 0;
-  return per_cu * cus;
-}
+constexpr size_t solve_lds_bytes(int nq, size_t elem) { return (size_t)(2 * kSB * kSB + 4 * nq * kSB) * elem; }
 
 // The substitution's workgroups wait on each other's blocks (bounded waits),
 // so the grid never exceeds what the device holds at once; like the panels it
 // is an ordinary launch unless ltlt_set_cooperative_panels(1) asks for the
 // runtime's cooperative one.
+template <typename T, bool UPPER, int NQ>
+hipError_t launch_solve_tri_q(const SolveTriArgs& a, hipStream_t s) {
+  const void* k = (const void*)solve_tri_kernel<T, UPPER, NQ>;
+  const size_t lds = solve_lds_bytes(NQ, sizeof(T));
+  hipError_t e = ensure_dynamic_lds(k, (int)lds);
+  if (e != hipSuccess) return e;
+  int dev = 0, per_cu = 0, cus = 0;
+  if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+  if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kSThreads, lds)) != hipSuccess) return e;
+  const int cap = per_cu * cus;
+  if (cap <= 0) return hipErrorInvalidValue;
+  return launch_resident_grid(solve_tri_kernel<T, UPPER, NQ>, (unsigned)(a.nblk < cap ? a.nblk : cap), kSThreads, lds,
+                              s, a);
+}
 template <typename T, bool UPPER>
 hipError_t launch_solve_tri(const SolveTriArgs& a, hipStream_t s) {
-  const int cap = solve_tri_max_blocks<T, UPPER>();
-  if (cap <= 0) return hipErrorInvalidValue;
-  const int grid = a.nblk < cap ? a.nblk : cap;
-  return launch_resident_grid(solve_tri_kernel<T, UPPER>, (unsigned)grid, kSThreads, 0, s, a);
+  if (a.nr == 1) return launch_solve_tri_q<T, UPPER, 1>(a, s);
+  if (a.nr == 2) return launch_solve_tri_q<T, UPPER, 2>(a, s);
+  return launch_solve_tri_q<T, UPPER, kSolveRhs>(a, s);
 }
 
 // Stamps of the mailbox words: a process-wide counter that skips 0 (zeroed
@@ -680,9 +684,9 @@ hipError_t launch_solve(int n, const T* A, int64_t lda, const int* ipiv, int nrh
   }
   T* Dinv = static_cast<T*>(w.dinv);
   T* Mf = Dinv + (size_t)nblk * kSB * kSB;
-  T* Mb = Mf + (size_t)kLook * nblk * kSB * kSB;
+  T* Mb = Mf + (size_t)nblk * kSB * kSB;
   hipLaunchKernelGGL(solve_dinv_kernel<T>, dim3(nblk), dim3(kWave), 0, s, A, lda, n, Dinv);
-  hipLaunchKernelGGL(solve_mmat_kernel<T>, dim3(nblk), dim3(2 * kLook * kWave), 0, s, A, lda, n, nblk, Dinv, Mf, Mb);
+  hipLaunchKernelGGL(solve_mmat_kernel<T>, dim3(nblk, 2), dim3(kSThreads), 0, s, A, lda, n, nblk, Dinv, Mf, Mb);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   for (int q0 = 0; q0 < nrhs; q0 += kSolveRhs) {
     const int nr = nrhs - q0 < kSolveRhs ? nrhs - q0 : kSolveRhs;
@@ -695,7 +699,7 @@ hipError_t launch_solve(int n, const T* A, int64_t lda, const int* ipiv, int nrh
     ta.box = w.box; ta.status = w.status; ta.Dinv = Dinv; ta.Mf = Mf; ta.Mb = Mb;
     ta.stamp = next_stamp();
     if ((e = launch_solve_tri<T, false>(ta, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(solve_tridiag_kernel<T>, dim3(1), dim3(2 * nr * kWave), 0, s, n, nr, alpha, ralpha, Y, W,
+    hipLaunchKernelGGL(solve_tridiag_kernel<T>, dim3(2 * nr), dim3(kTriWaves * kWave), 0, s, n, alpha, ralpha, Y, W,
                        w.ldy);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     ta.Y = W;

@@ -44,27 +44,6 @@ constexpr int kLd = kMT + 16;   // LDS row stride of an operand chunk (bank spre
 constexpr int kUpdateGrid = 768;   // persistent grid: three workgroups on each of 256 CUs
 constexpr int kUpdateWgPerCu = 3;
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-template <typename T> struct Mfma;
-template <> struct Mfma<double> {
-  typedef v4d acc_t;
-  static __device__ __forceinline__ acc_t run(double a, double b, acc_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  // output element v of lane l sits at row (l/16) + 4v, column l%16
-  static __device__ __forceinline__ int row(int l, int v) { return (l >> 4) + 4 * v; }
-};
-template <> struct Mfma<float> {
-  typedef v4f acc_t;
-  static __device__ __forceinline__ acc_t run(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  // output element v of lane l sits at row 4(l/16) + v, column l%16
-  static __device__ __forceinline__ int row(int l, int v) { return 4 * (l >> 4) + v; }
-};
-
 // One 128 x kKC chunk of an operand, thread -> column tid / kTpc, rows
 // (tid % kTpc) + kTpc e, e < kRpt: each load instruction reads kTpc
 // consecutive rows of a column, and each LDS store writes kTpc consecutive
