@@ -501,8 +501,8 @@ int factor_complex_impl(int64_t n64, void* A, int64_t lda, int32_t* ipiv, int nb
   const size_t o_LL = cv.take<T>((size_t)ldw * 3 * K0);
   const size_t o_BA = cv.take<T>((size_t)ldw * 2 * K0);
   const size_t o_BB = cv.take<T>((size_t)ldw * 2 * K0);
-  const size_t o_Gr = cv.take<T>((size_t)ldw * nb);
-  const size_t o_Gi = cv.take<T>((size_t)ldw * nb);
+  const size_t o_G = cv.take<T>((size_t)ldw * cpanel_g_cols(bw0));   // no block is wider than the first
+  const size_t o_tl = cv.take<T>(cpanel_tail_elems(bw0, ldw));
   const size_t o_Vr = cv.take<T>((size_t)ldw);
   const size_t o_Vi = cv.take<T>((size_t)ldw);
   const size_t o_ar = cv.take<T>((size_t)nb);
@@ -523,8 +523,8 @@ int factor_complex_impl(int64_t n64, void* A, int64_t lda, int32_t* ipiv, int nb
   T* LL = reinterpret_cast<T*>(base + o_LL);
   T* BA = reinterpret_cast<T*>(base + o_BA);
   T* BB = reinterpret_cast<T*>(base + o_BB);
-  T* Gr = reinterpret_cast<T*>(base + o_Gr);
-  T* Gi = reinterpret_cast<T*>(base + o_Gi);
+  T* Gm = reinterpret_cast<T*>(base + o_G);
+  T* tail = reinterpret_cast<T*>(base + o_tl);
   T* Vr = reinterpret_cast<T*>(base + o_Vr);
   T* Vi = reinterpret_cast<T*>(base + o_Vi);
   T* alr = reinterpret_cast<T*>(base + o_ar);
@@ -553,12 +553,12 @@ int factor_complex_impl(int64_t n64, void* A, int64_t lda, int32_t* ipiv, int nb
     pa.R = cpanel_rows(bw);
     pa.P = (m + pa.R - 1) / pa.R;
     pa.nrec = nrec;
-    pa.G = Gr; pa.ldw = ldw; pa.alpha = alr;
+    pa.G = Gm; pa.tail = tail; pa.ldw = ldw; pa.alpha = alr;
     pa.perm = Tblk + (int64_t)J * n;
     pa.ipiv = ipiv;
     pa.rec = rec;
     pa.status = status;
-    ca.Ai = Pi; ca.Gi = Gi; ca.Vr = Vr; ca.Vi = Vi;
+    ca.Ai = Pi; ca.Vr = Vr; ca.Vi = Vi;
     ca.LL = LL; ca.BtA = BA; ca.BtB = BB; ca.alpha_i = ali;
     {
       ProfScope ps(0, 0.0, s);

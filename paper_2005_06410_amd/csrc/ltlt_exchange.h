@@ -437,6 +437,77 @@ __device__ __forceinline__ XRes exchange_one(int k, int wave, int lane, const Ca
   return r;
 }
 
+// Buffer accesses; a lane whose offset is kSkip is out of
+// the buffer's range: its load returns 0 and its store is dropped, without a
+// branch, so that the waits for earlier loads count exactly the accesses
+// issued after them.
+constexpr unsigned kSkip = 0x80000000u;            // buffers are smaller than this
+// Buffer cache policy: device scope (sc1) between workgroups; within one, whose
+// waves share a CU and its L1, plain accesses (L2 hits instead of trips past it).
+template <bool ONE>
+constexpr int kPolicy = ONE ? 0 : 16;
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <typename T>
+struct Pair { T a, b; };
+template <bool ONE>
+__device__ __forceinline__ void buf_store2(double a, double b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Pair<double>{a, b}), rs, off, base, kPolicy<ONE>);
+}
+template <bool ONE>
+__device__ __forceinline__ void buf_store2(float a, float b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, Pair<float>{a, b}), rs, off, base, kPolicy<ONE>);
+}
+template <bool ONE>
+__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kPolicy<ONE>);
+}
+// 16 loaded bytes into v[at ..] (unless they lie past its n values).
+__device__ __forceinline__ void put16(double* v, int at, int n, u32x4 x) {
+  const auto d = __builtin_bit_cast(Pair<double>, x);
+  if (at < n) { v[at] = d.a; v[at + 1] = d.b; }
+}
+__device__ __forceinline__ void put16(float* v, int at, int n, u32x4 x) {
+  struct Four { float a, b, c, d; };
+  const auto f = __builtin_bit_cast(Four, x);
+  if (at < n) { v[at] = f.a; v[at + 1] = f.b; v[at + 2] = f.c; v[at + 3] = f.d; }
+}
+// One tail entry (two values).
+template <bool ONE>
+__device__ __forceinline__ Pair<double> buf_load2(double, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  return __builtin_bit_cast(Pair<double>, __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kPolicy<ONE>));
+}
+template <bool ONE>
+__device__ __forceinline__ Pair<float> buf_load2(float, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  return __builtin_bit_cast(Pair<float>, __builtin_amdgcn_raw_buffer_load_b64(rs, off, base, kPolicy<ONE>));
+}
+
+// Four values: one complex tail entry, or a lane's two complex g.
+template <bool ONE>
+__device__ __forceinline__ void buf_store4(double a, double b, double c, double d, __amdgpu_buffer_rsrc_t rs,
+                                           unsigned off, unsigned base) {
+  buf_store2<ONE>(a, b, rs, off, base);
+  buf_store2<ONE>(c, d, rs, off + 16, base);
+}
+template <bool ONE>
+__device__ __forceinline__ void buf_store4(float a, float b, float c, float d, __amdgpu_buffer_rsrc_t rs, unsigned off,
+                                           unsigned base) {
+  struct Four { float a, b, c, d; };
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Four{a, b, c, d}), rs, off, base, kPolicy<ONE>);
+}
+template <bool ONE>
+__device__ __forceinline__ void buf_load4(double (&v)[4], __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  const auto x = __builtin_bit_cast(Pair<double>, buf_load16<ONE>(rs, off, base));
+  const auto y = __builtin_bit_cast(Pair<double>, buf_load16<ONE>(rs, off + 16, base));
+  v[0] = x.a; v[1] = x.b; v[2] = y.a; v[3] = y.b;
+}
+template <bool ONE>
+__device__ __forceinline__ void buf_load4(float (&v)[4], __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
+  struct Four { float a, b, c, d; };
+  const auto x = __builtin_bit_cast(Four, buf_load16<ONE>(rs, off, base));
+  v[0] = x.a; v[1] = x.b; v[2] = x.c; v[3] = x.d;
+}
+
 // Workgroup barrier for LDS only: it waits for this wave's LDS operations
 // but not for its outstanding global loads (__syncthreads does, and with
 // them every tile and solution prefetch in flight).

@@ -24,7 +24,7 @@ struct PanelArgs {
   int P;              // workgroups
   int nrec;           // exchange records per slot (>= P of every block)
   void* G;            // what a pivot row hands to the others, one row per block-start index idx - j - 1
-  void* tail;         // real panel: the newest of these values, by step (panel_tail_elems)
+  void* tail;         // the newest of these values, by step (panel_tail_elems)
   void* PO;           // panel out, rows j+1.., columns 0..bw (bw = carry), ld = ldw
   void* Bm;           // Bt = Lx Tx^T for rows >= j+bw+1, columns 0..bw, ld = ldw
   int64_t ldw;
@@ -105,9 +105,8 @@ size_t panel_tail_elems(int bw, int64_t ldw);
 //   Re C += [Lr Li] [Btr -Bti]^T,   Im C += [Li Lr] [Btr Bti]^T,
 // with LL = [Lr Li Lr] holding both left operands as column windows.
 struct CPanelArgs {
-  PanelArgs b;        // A, G, alpha: real planes / parts; PO and Bm unused
+  PanelArgs b;        // A, alpha: real plane / parts; G and the tail hold complex values; PO and Bm unused
   const void* Ai;     // imaginary plane of the matrix (ld b.lda)
-  void* Gi;           // imaginary plane of the multiplier copy G
   void* Vr;           // pivot candidates' values by block-start index:
   void* Vi;           //   V[idx - j - 1] (real and imaginary parts)
   void* LL;           // [Lr | Li | Lr], K columns each, ld b.ldw, rows from j+1
@@ -116,6 +115,8 @@ struct CPanelArgs {
   void* alpha_i;      // imaginary parts of alpha_{j+t}
 };
 int cpanel_rows(int bw);
+int cpanel_g_cols(int bw);   // values per row of G
+size_t cpanel_tail_elems(int bw, int64_t ldw);
 template <typename T> size_t cpanel_lds_bytes(int bw);
 template <typename T> int cpanel_max_blocks(int bw, size_t lds);
 template <typename T> hipError_t launch_cpanel(const CPanelArgs& a, size_t lds, hipStream_t s);

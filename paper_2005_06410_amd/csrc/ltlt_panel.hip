@@ -113,51 +113,6 @@ template <int S>
 __device__ __forceinline__ int ring_at(int s) {
   return (s - 1) & (4 * S - 1);
 }
-// Buffer accesses; a lane whose offset is kSkip is out of
-// the buffer's range: its load returns 0 and its store is dropped, without a
-// branch, so that the waits for earlier loads count exactly the accesses
-// issued after them.
-constexpr unsigned kSkip = 0x80000000u;            // buffers are smaller than this
-// Buffer cache policy: device scope (sc1) between workgroups; within one, whose
-// waves share a CU and its L1, plain accesses (L2 hits instead of trips past it).
-template <bool ONE>
-constexpr int kPolicy = ONE ? 0 : 16;
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-template <typename T>
-struct Pair { T a, b; };
-template <bool ONE>
-__device__ __forceinline__ void buf_store2(double a, double b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Pair<double>{a, b}), rs, off, base, kPolicy<ONE>);
-}
-template <bool ONE>
-__device__ __forceinline__ void buf_store2(float a, float b, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, Pair<float>{a, b}), rs, off, base, kPolicy<ONE>);
-}
-template <bool ONE>
-__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  return __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kPolicy<ONE>);
-}
-// 16 loaded bytes into v[at ..] (unless they lie past its n values).
-__device__ __forceinline__ void put16(double* v, int at, int n, u32x4 x) {
-  const auto d = __builtin_bit_cast(Pair<double>, x);
-  if (at < n) { v[at] = d.a; v[at + 1] = d.b; }
-}
-__device__ __forceinline__ void put16(float* v, int at, int n, u32x4 x) {
-  struct Four { float a, b, c, d; };
-  const auto f = __builtin_bit_cast(Four, x);
-  if (at < n) { v[at] = f.a; v[at + 1] = f.b; v[at + 2] = f.c; v[at + 3] = f.d; }
-}
-// One tail entry (two values).
-template <bool ONE>
-__device__ __forceinline__ Pair<double> buf_load2(double, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  return __builtin_bit_cast(Pair<double>, __builtin_amdgcn_raw_buffer_load_b128(rs, off, base, kPolicy<ONE>));
-}
-template <bool ONE>
-__device__ __forceinline__ Pair<float> buf_load2(float, __amdgpu_buffer_rsrc_t rs, unsigned off, unsigned base) {
-  return __builtin_bit_cast(Pair<float>, __builtin_amdgcn_raw_buffer_load_b64(rs, off, base, kPolicy<ONE>));
-}
-
 // ONE: one workgroup holds every row (a.P == 1).
 template <typename T, int S, bool ONE>
 __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
