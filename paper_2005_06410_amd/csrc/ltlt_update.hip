@@ -329,12 +329,117 @@ __global__ void __launch_bounds__(kThreads, kUpdateWgPerCu) update_kernel(Update
   }
 }
 
+// Small trailing blocks: 64 x 64 tiles, one per workgroup.  128 x 128 tiles of a
+// block of order below 128 sqrt(2 CUs) leave CUs idle, and one such tile is a chain of
+// operand chunks, four gather rounds and barriers (30 us at any small order).
+// Here every wave loads the operands of its 32 x 32 sub-tile straight into registers
+// in the MFMA layout, eight steps of four columns ahead, the old values are
+// gathered before the contraction, and there are two barriers in all.  The
+// products are summed in the same order as in the 128 x 128 kernel (bit-identical).
+// Taken while the tiles give the CUs (256) at most two workgroups each, m <=
+// 1984.  Measured, 128 x 128 against this (us): fp64 K = 129 m = 300 30.7, 15.0, m =
+// 1919 43.9, 26.7, m = 2300 34.2, 36.9; K = 258 m = 1919 71.7, 39.2, m = 2300 54.2,
+// 54.7; fp32 K = 128 m = 1919 24.9, 15.5, m = 2700 25.5, 24.4.
+constexpr int kST = 64;                            // tile edge
+constexpr int64_t kSmallTiles = 512;               // two workgroups per CU
+constexpr int kSSteps = 8;                         // k-steps (four columns each) per register set
+template <typename T>
+__global__ void __launch_bounds__(kThreads) update_small_kernel(UpdateArgs a) {
+  typedef typename Mfma<T>::acc_t acc_t;
+  __shared__ T stage[kST * (kST + 1)];             // the tile's sums, [column][row]
+  __shared__ int prow[kST], pcol[kST];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, q = lane >> 4;
+  int J;
+  const int I = tri_index_decode(blockIdx.x, J);
+  const int r0 = I * kST, c0 = J * kST, m = a.m, K = a.K;
+  const int sr = (wave >> 1) * 32, sc = (wave & 1) * 32;   // the wave's sub-tile
+
+  // rows past m are clamped: they only feed outputs that are masked
+  const T* pa[2];
+  const T* pb[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    pa[x] = static_cast<const T*>(a.Lx) + min(r0 + sr + 16 * x + l16, m - 1);
+    pb[x] = static_cast<const T*>(a.Bt) + min(c0 + sc + 16 * x + l16, m - 1);
+  }
+  const int steps = (K + 3) / 4;
+  T af[2][kSSteps][2], bf[2][kSSteps][2];
+  auto load = [&](int s0, int set) {               // steps s0 .. s0+7; columns past K are clamped, zeroed below
+#pragma unroll
+    for (int e = 0; e < kSSteps; ++e) {
+      const int k = min(4 * (s0 + e) + q, K - 1);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        af[set][e][x] = pa[x][(int64_t)k * a.ldl];
+        bf[set][e][x] = pb[x][(int64_t)k * a.ldb];
+      }
+    }
+  };
+  load(0, 0);
+  if (tid < 2 * kST) {                             // sources, clamped as in the 128 x 128 kernel
+    const int at = (tid < kST ? r0 : c0) + (tid & (kST - 1));
+    const int src = (a.perm && at < m) ? min(max(a.perm[at] - a.perm_base, a.perm_lo), a.perm_hi) : at;
+    (tid < kST ? prow : pcol)[tid & (kST - 1)] = src;
+  }
+  __syncthreads();
+  // the wave finishes 16 columns of the tile, lane = row
+  T* C = static_cast<T*>(a.C);
+  const int64_t ldc = a.ldc;
+  const int i = r0 + lane;
+  T oldv[16];
+  gather_slice<T>(C, ldc, m, i, prow[lane], pcol, c0, 16 * wave, oldv);
+
+  acc_t acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) acc[x][y] = acc_t{0, 0, 0, 0};
+  auto use = [&](int s0, int set) {
+#pragma unroll
+    for (int e = 0; e < kSSteps; ++e) {
+      if (s0 + e >= steps) break;                  // uniform
+      const bool in = 4 * (s0 + e) + q < K;
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+          acc[x][y] = Mfma<T>::run(in ? af[set][e][x] : T(0), in ? bf[set][e][y] : T(0), acc[x][y]);
+    }
+  };
+  for (int s0 = 0; s0 < steps; s0 += 2 * kSSteps) {
+    load(s0 + kSSteps, 1);
+    use(s0, 0);
+    load(s0 + 2 * kSSteps, 0);
+    use(s0 + kSSteps, 1);
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        stage[(sc + 16 * y + l16) * (kST + 1) + sr + 16 * x + Mfma<T>::row(lane, v)] = acc[x][y][v];
+  __syncthreads();
+#pragma unroll
+  for (int cc = 0; cc < 16; ++cc) {
+    const int c = c0 + 16 * wave + cc;
+    if ((i > c) && (i < m)) C[(int64_t)i + (int64_t)c * ldc] = oldv[cc] + stage[(16 * wave + cc) * (kST + 1) + lane];
+  }
+}
+
 template <typename T>
 hipError_t launch_update(const UpdateArgs& a, hipStream_t s) {
   const int tiles = (a.m + kMT - 1) / kMT;
   const int64_t nblk = (int64_t)tiles * (tiles + 1) / 2;
   if (nblk <= 0) return hipSuccess;
   UpdateArgs c = a;
+  const int64_t st = ((int64_t)a.m + kST - 1) / kST, small = st * (st + 1) / 2;
+  if (small <= kSmallTiles && a.K > 0) {
+    hipLaunchKernelGGL((update_small_kernel<T>), dim3((unsigned)small), dim3(kThreads), 0, s, c);
+    return hipGetLastError();
+  }
   c.tiles = tiles;
   const int64_t grid = nblk < kUpdateGrid ? nblk : kUpdateGrid;
   // direct-to-LDS operand copies need 16-byte aligned column pairs and one
