@@ -484,7 +484,7 @@ __global__ __launch_bounds__(kThreads) void convgemm_direct_kernel(Geometry g, c
 // Small tiles keep the last round of the grid short and let few positions
 // (single images) fill the chip, and a 64 x 32 wave tile needs 12 loads per 32
 // MFMAs where the 32 x 64 wave tile of four waves side by side needs 20.
-// Measured (one box, GEMM M x N x K): AlexNet layer 4 at b = 80 (192 x 208080
+// Measured (GEMM M x N x K): AlexNet layer 4 at b = 80 (192 x 208080
 // x 1600) 1.13 -> 0.95 ms (134 TFLOP/s, 87 % of a large fp32 matrix product's
 // rate), layer 8 (256 x 9680 x 3456) 0.193 -> 0.136 ms, layer 7 at b = 1 (384
 // x 121 x 3456) 45 -> 15 us, 3 x 3 with padding 1 (384 x 11664 x 1728) 270 ->
@@ -693,6 +693,127 @@ __global__ __launch_bounds__(64 * WAVES) void convgemm_split_kernel(Geometry g, 
     }
 }
 
+// CONVGEMM by runs of taps (few channels, strided, no padding: first layers).
+// A lane's four contraction rows of a group are four taps y .. y + 3 of one
+// (x, c): contiguous in the input, so one 16-byte load replaces four (the
+// LDS-staged gather loads every element by itself, and at stride 4 each such
+// load spans four times the lines).  Where kh is not a multiple of four the last
+// run of a column starts at kh - 4, so that no load leaves its window, and its
+// first rows, which the run before it holds, are zeroed in both operands.  Lane
+// group q takes run 4 grp + q; a table of the runs' offsets is built in LDS when
+// the workgroup starts.  The waves of a workgroup split one 64 x 32 tile's runs,
+// as in the channel-block kernels.  What bounds it: three of a group's 16 taps
+// are zeros for kh = 11, and each lane's 16-byte loads still touch a line of
+// their own at stride 4.  Measured: AlexNet's first layer (64 x 93312 x 363,
+// stride 4) 59 -> 49 us, 16 x 16 patches (768 x 12544 x 768) 229 -> 129 us.
+struct Run {
+    uint32_t f, i;     // byte offsets of its first row in F and of its first tap in I
+    int skip;          // rows left out at its front: 0 to 3, or 4 past the last run
+    int pad;
+};
+template <int BM, int BN, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void convgemm_runs_kernel(Geometry g, const float* __restrict__ F,
+                                                                   const float* __restrict__ I, float* __restrict__ O,
+                                                                   int accumulate, int vec, int mtiles, int ntiles)
+{
+    static_assert(WAVES >= BN, "each column of the tile is stored by a wave of its own");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int nyq = (g.kh + 3) / 4, nruns = nyq * g.kw * g.ci, groups = (nruns + 3) / 4;
+    Run* runs = reinterpret_cast<Run*>(smem);
+    f4* part = reinterpret_cast<f4*>(smem + (size_t)groups * 4 * sizeof(Run));   // [WAVES][BN][BM][64]
+    for (int r = threadIdx.x; r < groups * 4; r += 64 * WAVES) {
+        Run v{kOutside, kOutside, 4, 0};
+        if (r < nruns) {
+            const int xc = r / nyq, y4 = 4 * (r - xc * nyq), y = min(y4, g.kh - 4), c = xc / g.kw, x = xc - c * g.kw;
+            v.f = (uint32_t)(y + g.kh * xc) * g.M * 4u;
+            v.i = (uint32_t)(y + g.hi * x + g.hiwi * c) * 4u;
+            v.skip = y4 - y;
+        }
+        runs[r] = v;
+    }
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int q = lane >> 4, l16 = lane & 15;
+    const int T = mtiles * ntiles, T8 = T & ~7, bid = blockIdx.x;
+    const int t = bid < T8 ? (bid & 7) * (T8 >> 3) + (bid >> 3) : bid;
+    const int m0 = (t % mtiles) * 16 * BM, n0 = (t / mtiles) * 16 * BN;
+    const __amdgpu_buffer_rsrc_t frs = tensor_rsrc(F, g.fbytes), irs = tensor_rsrc(I, g.ibytes);
+    // the filter count is a multiple of BM (the caller's rule: wide loads);
+    // filters and positions past the edge are clamped: they only feed outputs
+    // that are never stored
+    const uint32_t aoff = (uint32_t)min(m0 + BM * l16, g.M - BM) * 4u;
+    uint32_t coff[BN];
+#pragma unroll
+    for (int j = 0; j < BN; ++j) {
+        const int n = min(n0 + 16 * j + l16, g.N - 1);
+        const int nb = n / g.hw, rem = n - nb * g.hw, ow = rem / g.ho, oh = rem - ow * g.ho;
+        coff[j] = (uint32_t)(nb * g.sample + oh * g.s + (int64_t)g.hi * (ow * g.s)) * 4u;
+    }
+    f4 acc[BM][BN];
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int j = 0; j < BN; ++j) acc[i][j] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    float a[2][BM][4];
+    f4 b[2][BN];
+    int skip[2];
+    auto load = [&](int grp, int set) {
+        const Run r = runs[4 * grp + q];
+        skip[set] = r.skip;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const uint32_t row = r.f + (uint32_t)kk * g.M * 4u;
+            load_filters<BM>(a[set], kk, frs, kk >= r.skip ? aoff + row : kOutside, 0u);
+        }
+#pragma unroll
+        for (int j = 0; j < BN; ++j)
+            b[set][j] = __builtin_bit_cast(
+                f4, __builtin_amdgcn_raw_buffer_load_b128(irs, (int)(r.skip < 4 ? coff[j] + r.i : kOutside), 0, 0));
+    };
+    auto compute = [&](int set) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            float bv[BN];
+#pragma unroll
+            for (int j = 0; j < BN; ++j) bv[j] = kk >= skip[set] ? b[set][j][kk] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < BM; ++i)
+#pragma unroll
+                for (int j = 0; j < BN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[set][i][kk], bv[j], acc[i][j], 0, 0, 0);
+        }
+    };
+    int grp = wave * groups / WAVES;
+    const int ghi = (wave + 1) * groups / WAVES;
+    if (grp < ghi) load(grp, 0);
+    for (; grp + 2 <= ghi; grp += 2) {
+        load(grp + 1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (grp + 2 < ghi) load(grp + 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (grp < ghi) compute(0);
+#pragma unroll
+    for (int j = 0; j < BN; ++j)
+#pragma unroll
+        for (int i = 0; i < BM; ++i) part[((wave * BN + j) * BM + i) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    if (wave < BN) {
+        f4 v[BM];
+#pragma unroll
+        for (int i = 0; i < BM; ++i) {
+            v[i] = part[(wave * BM + i) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) v[i] += part[((w * BN + wave) * BM + i) * 64 + lane];
+        }
+        store_column<BM>(O, g, m0 + 4 * BM * q, n0 + 16 * wave + l16, v, accumulate, vec);
+    }
+}
+
 int out_size(int h, int k, int s, int p)
 {
     if (k < 1 || s < 1 || p < 0 || h < 1) return -1;
@@ -804,6 +925,23 @@ hipError_t launch_split(const Geometry& g, const float* F, const float* I, float
     else if (g.p == 0) go(convgemm_split_kernel<BM, BN, false, false, WAVES>);
     else if (veca) go(convgemm_split_kernel<BM, BN, true, true, WAVES>);
     else go(convgemm_split_kernel<BM, BN, true, false, WAVES>);
+    return hipGetLastError();
+}
+
+// runs of four taps in a contraction
+size_t run_count(const Geometry& g) { return (size_t)((g.kh + 3) / 4) * g.kw * g.ci; }
+
+template <int BM, int BN, int WAVES>
+hipError_t launch_runs(const Geometry& g, const float* F, const float* I, float* O, int accumulate, int vec,
+                       hipStream_t stream)
+{
+    const int mtiles = (g.M + 16 * BM - 1) / (16 * BM), ntiles = (g.N + 16 * BN - 1) / (16 * BN);
+    const int64_t tiles = (int64_t)mtiles * ntiles;
+    if (tiles > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const size_t lds = (run_count(g) + 3) / 4 * 4 * sizeof(Run) + (size_t)WAVES * BN * BM * 64 * sizeof(f4);
+    const dim3 grid((unsigned)tiles), block(64 * WAVES);
+    hipLaunchKernelGGL((convgemm_runs_kernel<BM, BN, WAVES>), grid, block, lds, stream, g, F, I, O, accumulate, vec,
+                       mtiles, ntiles);
     return hipGetLastError();
 }
 
@@ -933,6 +1071,22 @@ extern "C" int convgemm_f32(int kn, int kh, int kw, int ci, int hi, int wi, int 
     if (path == 0 && (ci + 15) / 16 * 16 * 2 <= 3 * ci && !(ci % 16 != 0 && direct && large) &&
         g.ibytes <= kOutside && g.fbytes <= kOutside) {
         e = launch_channel_blocks(g, F, I, O, accumulate, vec, cus, stream);
+        return e == hipSuccess ? CONVGEMM_OK : CONVGEMM_ERR_HIP_BASE - (int)e;
+    }
+    // few channels, strided and not padded, a tap height that runs of four cover
+    // with at most a third of waste, filters in wide loads, and a contraction of
+    // at least 64 taps whose table fits LDS: the runs kernel.  Old path against it:
+    // kh = 5 (two runs for five taps, 64 x 14400 x 250) 13 against 17 us, an odd
+    // filter count (33 x 61504 x 75) 16 against 21, 48 taps (384 x 63504) 39
+    // against 39; stride 1 (7 x 7, 64 x 131072 x 147) 31 against 35, where the
+    // register-direct kernel reads contiguous runs already.  Four waves share the
+    // contraction from 16 groups on (64 x 46656 x 363: 33 us before, 31 with two
+    // waves, 26 with four), two below (64 x 190096 x 147: 52, 46, 49).
+    const size_t nruns = run_count(g);
+    if (path == 0 && pad == 0 && stride > 1 && kn % 4 == 0 && kh >= 4 && kh != 5 && nruns >= 16 && nruns <= 2048 &&
+        g.ibytes <= kOutside && g.fbytes <= kOutside) {
+        e = nruns > 60 ? launch_runs<4, 2, 4>(g, F, I, O, accumulate, vec, stream)
+                       : launch_runs<4, 2, 2>(g, F, I, O, accumulate, vec, stream);
         return e == hipSuccess ? CONVGEMM_OK : CONVGEMM_ERR_HIP_BASE - (int)e;
     }
     // otherwise the register-direct kernel for unit-stride convolutions
