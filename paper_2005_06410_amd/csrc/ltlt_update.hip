@@ -309,6 +309,26 @@ __global__ void __launch_bounds__(kThreads, kUpdateWgPerCu) update_kernel(Update
   constexpr int kEp = 65;                          // padded column stride in LDS
   static_assert(4 * 16 * kEp <= 4 * kKC * kLd, "epilogue staging must fit the operand LDS");
   T* stage = lds + wave * (16 * kEp);              // 16 columns x 65 per wave
+  // Tiles strictly below the diagonal and inside the block (inner): lane = row, so
+  // the old values of one column are one run of memory from S(pr, c) on, stepping
+  // by ldc from column to column, except in lanes whose row comes from before the
+  // block (a displaced row), which step along row pr's column with the sign
+  // turned.  One running address and one sign per lane then serve all columns but
+  // the displaced ones (mcols; 1 % at m = 16256), which are looked up one by one.
+  // The general gather forms a 64-bit address, a mask and a sign for every entry,
+  // vector work that the other waves' MFMAs wait for.  Measured, general against
+  // this (us, bit-identical): fp64 K = 129 m = 16256 776, 750, m = 8000
+  // 209, 200, m = 2300 35, 35; fp32 K = 128 m = 16256 449, 393, m = 4000 45, 42.
+  // The register-staged fp64 kernel keeps the general form: it spills more with
+  // both (m = 2003 44 against 52 us).
+  const int cw = c0 + wc * 64;                     // the wave's columns
+  constexpr bool kInner = DMA || sizeof(T) == 4;
+  const bool inner = kInner && r0 >= c0 + kMT && r0 + kMT <= m && __ballot(pr >= c0 && pr < r0) == 0;
+  const unsigned long long mcols = __ballot(pcol[wc * 64 + lane] != cw + lane);
+  const bool low = pr >= r0;
+  const T sgn = low ? T(1) : T(-1);
+  const T* src = low ? C + pr + (int64_t)cw * ldc : C + cw + (int64_t)pr * ldc;
+  const int64_t sstep = low ? ldc : 1;
 #pragma unroll
   for (int y = 0; y < 4; ++y) {
 #pragma unroll
@@ -318,11 +338,38 @@ __global__ void __launch_bounds__(kThreads, kUpdateWgPerCu) update_kernel(Update
         stage[(lane & 15) * kEp + x * 16 + Mfma<T>::row(lane, v)] = acc[x][y][v];
     __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0): this wave's LDS writes done
     T oldv[16];
-    gather_slice<T>(C, ldc, m, i, pr, pcol, c0, wc * 64 + y * 16, oldv);
+    if (inner) {
+      const unsigned moved = (unsigned)(mcols >> (16 * y)) & 0xffffu;
+      unsigned flip = 0;
 #pragma unroll
-    for (int cc = 0; cc < 16; ++cc) {
-      const int c = c0 + wc * 64 + y * 16 + cc;
-      if ((i > c) && (i < m)) C[(int64_t)i + (int64_t)c * ldc] = oldv[cc] + stage[cc * kEp + lane];
+      for (int cc = 0; cc < 16; ++cc) {
+        const T* at = src;
+        if (moved & (1u << cc)) {
+          const int pc = __builtin_amdgcn_readfirstlane(pcol[wc * 64 + y * 16 + cc]);
+          const bool plow = pr > pc;
+          at = C + (plow ? (int64_t)pr + (int64_t)pc * ldc : (int64_t)pc + (int64_t)pr * ldc);
+          flip |= plow != low ? 1u << cc : 0u;
+        }
+        oldv[cc] = *at;
+        src += sstep;
+      }
+      if (moved) {
+#pragma unroll
+        for (int cc = 0; cc < 16; ++cc) oldv[cc] = flip & (1u << cc) ? -oldv[cc] : oldv[cc];
+      }
+      T* dst = C + (int64_t)(cw + y * 16) * ldc + (r0 + wr * 64);
+#pragma unroll
+      for (int cc = 0; cc < 16; ++cc) {
+        dst[(unsigned)lane] = fma(sgn, oldv[cc], stage[cc * kEp + lane]);
+        dst += ldc;
+      }
+    } else {
+      gather_slice<T>(C, ldc, m, i, pr, pcol, c0, wc * 64 + y * 16, oldv);
+#pragma unroll
+      for (int cc = 0; cc < 16; ++cc) {
+        const int c = c0 + wc * 64 + y * 16 + cc;
+        if ((i > c) && (i < m)) C[(int64_t)i + (int64_t)c * ldc] = oldv[cc] + stage[cc * kEp + lane];
+      }
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);            // reads of this slice done before it is overwritten
   }

@@ -2,7 +2,9 @@
 order 1984, 128 x 128 beyond) and of their tiles and steps, against the same
 product in fp64: C(i, c) = S(perm i, perm c) + sum_u Lx(i, u) Bt(c, u) below the
 diagonal, sources before the block, everything else untouched.  Operands with
-odd leading dimensions take the 128 x 128 kernel's register-staged loads.  Bar:
+odd leading dimensions take the 128 x 128 kernel's register-staged loads; rows
+and columns held before the block fall into tiles inside the block, on its
+diagonal and at its edge.  Bar:
 gamma_{K+1} (|S| + |Lx| |Bt|^T) entrywise (any order of the sums)."""
 from __future__ import annotations
 
@@ -15,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("m,K,odd", [(2, 1, 0), (63, 4, 1), (64, 5, 0), (65, 31, 0), (129, 33, 1), (200, 129, 0),
-                                     (700, 130, 1), (1984, 36, 0), (1985, 36, 0), (1985, 37, 1), (2111, 129, 0)])
+                                     (700, 130, 1), (1984, 36, 0), (1985, 36, 0), (1985, 37, 1), (2111, 129, 0), (2304, 20, 0)])
 def test_update_sizes(m, K, odd, dtype):
     import paper_2005_06410_amd as lt
     g = torch.Generator(device="cuda")
