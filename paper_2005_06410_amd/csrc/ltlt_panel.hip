@@ -82,8 +82,8 @@
 // What bounds it: the step is one dependency chain (clock stamps, cycles, n =
 // 16384 / n = 256): publish, poll and reduction of the records 3650 / 2640, the
 // pivot row's values and the stored column 1000 / 600, everything local about
-// 2300.  With the values handed out as above a step takes 4.17 -> 3.0 us at
-// n = 16384 (factorization 97.4 -> 87.5 ms) and 2.6 -> 2.2 us at n = 2048
+// 2300.  With the values handed out as above a step takes 3.6 -> 3.0 us at
+// n = 16384 (factorization 97.4 -> 87.5 ms) and 2.9 -> 2.4 us at n = 2048
 // (6.68 -> 5.57 ms), outputs bit-identical.
 
 #include "ltlt_device.h"
