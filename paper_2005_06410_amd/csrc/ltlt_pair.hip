@@ -103,7 +103,10 @@ __device__ __forceinline__ T wave_sum(T v) {
 
 int pair_panel_rows(int bw) { return (kPanelWaves - 1) * (kWave / panel_split(bw)); }
 
-template <typename T, int S>
+// ONE: one workgroup holds every row and agrees in LDS (P = 1; measured, agreement
+// through a record against this, us, bit-identical: fp64 n = 100 189, 176, n = 224
+// 444, 416; fp32 n = 160 274, 263).
+template <typename T, int S, bool ONE>
 __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int R = (kPanelWaves - 1) * (kWave / S);
@@ -130,7 +133,7 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
   T* bufQ = bufB + TOT;                            // slots of row q
   T* gcol = bufQ + TOT;                            // g of the current column, by slot
   __shared__ XRes s_x;
-  __shared__ Cand red[kPanelWaves];
+  __shared__ Cand red[ONE ? 2 : 1][kPanelWaves];   // two sets in turn: a slow reader of the last step's
 
   const int row0 = j + 1 + w * R;
   const int rows_here = max(0, min(R, n - row0));
@@ -176,10 +179,10 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
     // ---- pivot candidate of column k ----
     {
       const double m = (double)fabs(cv);
-      wave_candidate(red, wave, make_cand(active && part == 0 && m == m, m, cv < T(0), pos, lp));
+      wave_candidate(red[ONE ? t & 1 : 0], wave, make_cand(active && part == 0 && m == m, m, cv < T(0), pos, lp));
     }
     const int stamp = k / 2 + 1;
-    exchange_publish(a, stamp, wave, lane, w, red);
+    if constexpr (!ONE) exchange_publish(a, stamp, wave, lane, w, red[0]);
 
     // ---- column k+2 for the row qq at position k+2 (independent of the
     //      pivot unless it comes from k+2): its slots, S(pos, qq), cA = column
@@ -228,8 +231,13 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
     const int displaced = lookup(k + 1);           // row at position k+1 before the exchange
     if (!last && rowwave) spec(qs);
 
-    exchange_collect(a, stamp, k, wave, lane, s_x, [](int) {});
-    const XRes xr = s_x;
+    XRes xr;
+    if constexpr (ONE) {
+      xr = exchange_one(k, wave, lane, red[t & 1], [](int) {});
+    } else {
+      exchange_collect(a, stamp, k, wave, lane, s_x, [](int) {});
+      xr = s_x;
+    }
     const int p = xr.p;
     const int posw = xr.posw;
     const T alph = (T)xr.alpha;
@@ -383,7 +391,8 @@ __global__ void __launch_bounds__(kPanelThreads, 1) pair_panel_kernel(PanelArgs 
 
 template <typename T, int S>
 hipError_t launch_pair_panel_s(const PanelArgs& a, size_t lds, hipStream_t st) {
-  return launch_resident_grid(pair_panel_kernel<T, S>, (unsigned)a.P, kPanelThreads, lds, st, a);
+  if (a.P == 1) return launch_resident_grid(pair_panel_kernel<T, S, true>, 1u, kPanelThreads, lds, st, a);
+  return launch_resident_grid(pair_panel_kernel<T, S, false>, (unsigned)a.P, kPanelThreads, lds, st, a);
 }
 
 template <typename T>
@@ -403,7 +412,7 @@ int pair_max_blocks_s(size_t lds) {
   int dev = 0, per_cu = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)pair_panel_kernel<T, S>, kPanelThreads,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)pair_panel_kernel<T, S, false>, kPanelThreads,
                                                    lds) != hipSuccess)
     return 0;
   return per_cu * cus;
