@@ -32,11 +32,12 @@
  * single precision), products and sums on the fp32 matrix cores; the order of
  * the sums is unspecified, so results agree with an exact evaluation within
  * the usual fp32 bound |error| <= gamma_K * sum |F| |I| (K = kh kw ci), and are
- * exact whenever every partial sum is an integer below 2^24.  For short
- * grids with long contractions the automatic choice splits a tile's
- * contraction over several workgroups that add into O atomically, so the
- * last bits of such a call may differ from one run to the next.  O may not
- * overlap F or I.
+ * exact whenever every partial sum is an integer below 2^24.  The
+ * register-direct kernel (path 2, or path 0 where convgemm_choice says so: most
+ * often few channels, unit stride, no padding) splits the contractions of short
+ * grids with long contractions over several workgroups that add into O
+ * atomically, so the last bits of such a call may differ from one run to the
+ * next; every other call is reproducible.  O may not overlap F or I.
  */
 #ifndef CONVGEMM_H
 #define CONVGEMM_H
@@ -82,6 +83,17 @@ int convgemm_out_size(int h, int k, int stride, int pad);
 int convgemm_f32(int kn, int kh, int kw, int ci, int hi, int wi, int b, int stride, int pad,
                  const float* F, const float* I, float* O, int accumulate, int path, int mt, int nt,
                  hipStream_t stream);
+
+/* The kernel that path = 0 takes for a layer (host only; arguments and return
+ * value as convgemm_f32, out = NULL is argument 10).  HOST int out[4]:
+ *   out[0] = 1 LDS-staged gather, 2 register-direct, 3 channel blocks (16
+ *            channels of one tap at a time), 4 runs of taps (four taps of a
+ *            column at a time); 0 when b = 0;
+ *   out[1], out[2] = its tile, filters x output positions;
+ *   out[3] = workgroups (register-direct: atomic adds when above 1) or waves of
+ *            a workgroup (3, 4: added in a fixed order) that share one tile's
+ *            contraction. */
+int convgemm_choice(int kn, int kh, int kw, int ci, int hi, int wi, int b, int stride, int pad, int* out);
 
 #ifdef __cplusplus
 }

@@ -83,6 +83,7 @@ _SYMBOLS = {
                     ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p], ctypes.c_int),
     # include/convgemm.h
     "convgemm_out_size": ([ctypes.c_int] * 4, ctypes.c_int),
+    "convgemm_choice": ([ctypes.c_int] * 9 + [ctypes.c_void_p], ctypes.c_int),
     "convgemm_f32": ([ctypes.c_int] * 9 + [ctypes.c_void_p] * 3 + [ctypes.c_int] * 4 + [ctypes.c_void_p],
                      ctypes.c_int),
 }
@@ -368,6 +369,15 @@ def conv_out_size(h: int, k: int, stride: int = 1, pad: int = 0) -> int:
     if r < 1:
         raise ValueError(f"no output for h={h} k={k} stride={stride} pad={pad}")
     return r
+
+
+def conv_choice(kn: int, kh: int, kw: int, ci: int, hi: int, wi: int, b: int, stride: int = 1, pad: int = 0):
+    """The kernel that ``convgemm`` takes by itself for a layer, as (family,
+    mt, nt, share): see ``convgemm_choice``.  Host only."""
+    out = (ctypes.c_int * 4)()
+    code = load().convgemm_choice(*(int(v) for v in (kn, kh, kw, ci, hi, wi, b, stride, pad)), ctypes.addressof(out))
+    _check("convgemm_choice", code)
+    return tuple(out)
 
 
 def _leftmost_fastest(t, name):

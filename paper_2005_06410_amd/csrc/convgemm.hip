@@ -945,42 +945,204 @@ hipError_t launch_runs(const Geometry& g, const float* F, const float* I, float*
     return hipGetLastError();
 }
 
+// What is launched: the kernel family (the codes of convgemm_choice), its tile,
+// and how many workgroups (register-direct) or waves of a workgroup (channel
+// blocks, runs) share one tile's contraction.
+enum Family { kStaged = 1, kDirect = 2, kBlocks = 3, kRuns = 4 };
+struct Choice {
+    int family, mt, nt, share;
+};
+
+int64_t tile_count(const Geometry& g, int mt, int nt)
+{
+    return (int64_t)((g.M + mt - 1) / mt) * ((g.N + nt - 1) / nt);
+}
+
+// Register-direct tile, measured on the AlexNet layers: 64 x 128 while that
+// still gives four tiles per CU; 128 x 64 for filter counts divisible by 128
+// with at least 1.5 tiles per CU; 64 x 64 otherwise.  Grids short even with the
+// smallest tile, and long contractions: the contraction of each tile is split
+// over several workgroups (atomic adds into O) so that every CU holds about
+// three, each part keeping at least 64 groups of 16.
+Choice direct_choice(const Geometry& g, int cus)
+{
+    if (tile_count(g, 64, 128) >= 4 * (int64_t)cus) return Choice{kDirect, 64, 128, 1};
+    if (g.M % 128 == 0 && 2 * tile_count(g, 128, 64) >= 3 * (int64_t)cus) return Choice{kDirect, 128, 64, 1};
+    int kparts = 1;
+    const int64_t tl = tile_count(g, 64, 64);
+    const int ngroups = (g.K + 15) / 16;
+    while (kparts < 4 && tl * kparts < 3 * (int64_t)cus && ngroups / (2 * kparts) >= 64) kparts *= 2;
+    return Choice{kDirect, 64, 64, kparts};
+}
+
+Choice staged_choice(const Geometry& g, int cus)
+{
+    const Tile t = choose_tile(g.M, g.N, cus);
+    return Choice{kStaged, t.mt, t.nt, 1};
+}
+
 // Tile and split of the channel-block kernels, by the estimated time of the
 // grid: rounds of tiles over the CUs, times the tile's size, over the share of
 // the matrix rate that the tile shape reached in measurements of 21 layers
 // (GEMM N from 121 to 208080, K from 64 to 12544; the model's choice was within
 // 7 % of the best shape on each).  Wide loads of the filters need kn to be a
 // multiple of BM, which costs the 64-filter tiles most.
-hipError_t launch_channel_blocks(const Geometry& g, const float* F, const float* I, float* O, int accumulate, int vec,
-                                 int cus, hipStream_t stream)
+Choice blocks_choice(const Geometry& g, int cus)
 {
     const int groups = tap_groups(g);
-    auto tiles = [&](int mt, int nt) { return (int64_t)((g.M + mt - 1) / mt) * ((g.N + nt - 1) / nt); };
     auto cost = [&](int mt, int nt, double rate) {
-        return (double)((tiles(mt, nt) + cus - 1) / cus) * mt * nt / rate;
+        return (double)((tile_count(g, mt, nt) + cus - 1) / cus) * mt * nt / rate;
     };
     // eight or fewer groups: one wave's worth, four tiles side by side instead
     // (256 x 100352 x 64: 43 against 54 us) while they fill the chip
-    if (groups <= 8 && tiles(64, 128) >= 4 * (int64_t)cus)
-        return launch_square<2, 4>(g, F, I, O, accumulate, vec, stream);
+    if (groups <= 8 && tile_count(g, 64, 128) >= 4 * (int64_t)cus) return Choice{kBlocks, 64, 128, 1};
     const double wide = g.M % 4 == 0 ? 0.85 : 0.55;
     const double c42 = cost(64, 32, wide), c41 = cost(64, 16, wide - 0.10), c22 = cost(32, 32, g.M % 2 == 0 ? 0.68 : 0.62),
                  c24 = cost(32, 64, 0.72), c11 = cost(16, 16, 0.42);
     const double best = std::min({c42, c41, c22, c24, c11});
     // eight waves instead of four where that many more are needed to cover the
     // loads' latency: few tiles per CU, long contractions
-    if (c42 == best) {
-        if (groups >= 64 && tiles(64, 32) < 6 * (int64_t)cus)
-            return launch_split<4, 2, 8>(g, F, I, O, accumulate, vec, stream);
-        return launch_split<4, 2, 4>(g, F, I, O, accumulate, vec, stream);
+    if (c42 == best)
+        return Choice{kBlocks, 64, 32, groups >= 64 && tile_count(g, 64, 32) < 6 * (int64_t)cus ? 8 : 4};
+    if (c41 == best) return Choice{kBlocks, 64, 16, tile_count(g, 64, 16) <= 2 * (int64_t)cus ? 8 : 4};
+    if (c22 == best) return Choice{kBlocks, 32, 32, 8};
+    if (c24 == best) return Choice{kBlocks, 32, 64, 8};
+    return Choice{kBlocks, 16, 16, 16};
+}
+
+// Estimated time of a choice in microseconds, to compare the channel-block
+// kernels with the general ones: rounds of tiles over the CUs, each a fixed part
+// (`tile`) and a part per 16 rows of the contraction (`group`), slower where
+// filters are loaded one by one (`narrow`), where padding is checked per element
+// (`pad`) and where neighbouring positions lie apart in the input (`strided`);
+// `store` is added per MB of outputs stored one by one (kn no multiple of 4); at
+// least a launch's latency and the tensors' traffic (10 TB/s, caches included).
+// The constants are fits to the times of every kernel on 13130 layers (kn 1 to
+// 1500, K 11 to 124000, N 1 to 2.4 10^6; errors of 4 to 19 % root mean square).
+struct Rate {
+    int family, mt, nt, share;
+    double tile, group, narrow, pad, strided, store;
+};
+constexpr Rate kRates[] = {
+    {kBlocks, 64, 128, 1, 1.08, 0.631, 0.11, 0, 0.058, 0.53}, {kBlocks, 64, 32, 4, 0.63, 0.151, 0.69, 0, 0.039, 0.67},
+    {kBlocks, 64, 32, 8, 1.39, 0.138, 0.69, 0, 0.036, 0.63},  {kBlocks, 64, 16, 4, 0.27, 0.084, 0.99, 0, 0.063, 0.85},
+    {kBlocks, 64, 16, 8, 0.63, 0.080, 1.05, 0, 0.048, 0.61},  {kBlocks, 32, 32, 8, 0.61, 0.085, 0.29, 0, 0.115, 0.18},
+    {kBlocks, 32, 64, 8, 1.48, 0.156, 0.13, 0, 0.096, 0.29},  {kBlocks, 16, 16, 16, 0.87, 0.037, 0, 0, 0.125, 0.28},
+    {kDirect, 64, 128, 1, 1.43, 0.534, 0, 0, 0, 0.31},        {kDirect, 128, 64, 1, 1.70, 0.561, 0, 0, 0, 0.30},
+    {kDirect, 64, 64, 1, 0.31, 0.369, 0, 0, 0, 0.42},         {kStaged, 128, 128, 1, 2.19, 1.217, 0, 0.17, 0, 0.30},
+};
+// its contraction shared with atomic adds; the LDS-staged 64 x 64 tile in chunks
+// of 32 (short grids) and 16 rows
+constexpr Rate kDirectShared = {kDirect, 64, 64, 0, 0.68, 0.372, 0, 0, 0, 1.56};
+constexpr Rate kStagedLong = {kStaged, 64, 64, 1, 0.36, 0.463, 0, 0.31, 0, 0.34};
+constexpr Rate kStagedShort = {kStaged, 64, 64, 1, 0.54, 0.373, 0, 0.26, 0, 0.24};
+
+double estimate(const Geometry& g, const Choice& c, int cus)
+{
+    const int64_t tiles = tile_count(g, c.mt, c.nt) * (c.family == kDirect ? c.share : 1);
+    const Rate* r = &kRates[0];
+    if (c.family == kDirect && c.share > 1) r = &kDirectShared;
+    else if (c.family == kStaged && c.mt == 64) r = tiles < 4 * (int64_t)cus ? &kStagedLong : &kStagedShort;
+    else
+        for (const Rate& x : kRates)
+            if (x.family == c.family && x.mt == c.mt && x.nt == c.nt && x.share == c.share) r = &x;
+    const bool blocks = c.family == kBlocks;
+    const double groups = blocks ? tap_groups(g) : (double)((g.K + 15) / 16) / (c.family == kDirect ? c.share : 1);
+    const int wide = c.nt == 128 ? 2 : c.mt / 16;            // filters a lane loads at once
+    double slow = 1.0 + (g.p > 0 ? r->pad : 0.0);
+    if (blocks && g.M % wide != 0) slow += r->narrow;
+    if (g.s > 1) slow *= 1.0 + r->strided * (g.s - 1 + std::max(0.0, 16.0 / g.ho - 1.0));
+    const double used = 0.85 + 0.15 * std::min(g.M, c.mt) / c.mt;   // filters past kn load the same bytes
+    const double out_mb = 4e-6 * g.M * (double)g.N;
+    double work = (double)((tiles + cus - 1) / cus) * (r->tile + r->group * groups * slow * used);
+    if (g.M % 4 != 0) work += r->store * out_mb;
+    double lat = 5.2;
+    if (c.family == kStaged) lat = 3.0 + (r == &kStagedLong ? 0.54 : 1.5) * groups;
+    if (blocks && c.share == 1) lat += 0.5 * groups;
+    if (r == &kDirectShared) work += 1.6 * out_mb + 4.0;             // O cleared first, then atomic adds
+    const double mem = 0.1 * (1e-6 * ((double)g.ibytes + (double)g.fbytes) + out_mb);
+    return std::max({work, lat, mem});
+}
+
+// The automatic choice.
+Choice choose(const Geometry& g, int cus)
+{
+    // without padding and at unit stride the register-direct kernel (the im2col
+    // columns of neighbouring positions are then contiguous input runs that the
+    // caches serve well); the LDS-staged gather otherwise (measured: the direct
+    // kernel is slower at stride 4, where each load instruction spans four times
+    // the lines) and for contractions longer than the direct kernel's row table
+    const bool direct = g.p == 0 && g.s == 1 && g.K <= kDirectMaxK;
+    const Choice general = direct ? direct_choice(g, cus) : staged_choice(g, cus);
+    if (g.ibytes > kOutside || g.fbytes > kOutside) return general;
+    // enough channels that blocks of 16 waste no more than a third of the
+    // products (three channels would run at a fifth): the channel-block kernels.
+    // With whole blocks, wide filter loads and more than 16 groups they are the
+    // faster ones (2379 measured layers: 0.30 of the general kernel's time in the
+    // mean, none slower by more than 12 %).  Elsewhere the estimates decide: a
+    // contraction of a few groups leaves the waves that share a tile without work
+    // (16 x 125440 x 16: 35 against 7.5 us general), partial blocks and filters
+    // loaded one by one cost too much on many tiles (33 x 125440 x 64: 35 against
+    // 20), and so do wide strides (870 x 2700 x 3456, stride 4: 378 against 249).
+    // Over 13130 measured layers the blocks alone took 0.515 of the general
+    // kernels' time in the mean but were slower by more than 4 % on 1207 of them;
+    // with this rule 0.501, and on 127.  With a partial block and a large unpadded
+    // grid at unit stride the register-direct kernel, which wastes no products, is
+    // faster (256 x 102660 x 297, 33 channels: 144 against 217 us).
+    const bool large = tile_count(g, 64, 128) >= 4 * (int64_t)cus;
+    if ((g.ci + 15) / 16 * 16 * 2 <= 3 * g.ci) {
+        if (g.ci % 16 != 0 && direct && large) return general;
+        const Choice blocks = blocks_choice(g, cus);
+        if (g.ci % 16 == 0 && g.M % 4 == 0 && tap_groups(g) > 16) return blocks;
+        return estimate(g, general, cus) < estimate(g, blocks, cus) ? general : blocks;
     }
-    if (c41 == best) {
-        if (tiles(64, 16) <= 2 * (int64_t)cus) return launch_split<4, 1, 8>(g, F, I, O, accumulate, vec, stream);
-        return launch_split<4, 1, 4>(g, F, I, O, accumulate, vec, stream);
+    // few channels, strided and not padded, a tap height that runs of four cover
+    // with at most a third of waste, filters in wide loads, and a contraction of
+    // at least 64 taps whose table fits LDS: the runs kernel.  Old path against it:
+    // kh = 5 (two runs for five taps, 64 x 14400 x 250) 13 against 17 us, an odd
+    // filter count (33 x 61504 x 75) 16 against 21, 48 taps (384 x 63504) 39
+    // against 39; stride 1 (7 x 7, 64 x 131072 x 147) 31 against 35, where the
+    // register-direct kernel reads contiguous runs already.  Four waves share the
+    // contraction from 16 groups on (64 x 46656 x 363: 33 us before, 31 with two
+    // waves, 26 with four), two below (64 x 190096 x 147: 52, 46, 49).
+    const size_t nruns = run_count(g);
+    if (g.p == 0 && g.s > 1 && g.M % 4 == 0 && g.kh >= 4 && g.kh != 5 && nruns >= 16 && nruns <= 2048)
+        return Choice{kRuns, 64, 32, nruns > 60 ? 4 : 2};
+    return general;
+}
+
+hipError_t launch_choice(const Geometry& g, const Choice& c, const float* F, const float* I, float* O, int accumulate,
+                         int vec, int cus, hipStream_t stream)
+{
+    switch (c.family) {
+    case kBlocks:
+        if (c.nt == 128) return launch_square<2, 4>(g, F, I, O, accumulate, vec, stream);
+        if (c.mt == 64 && c.nt == 32)
+            return c.share == 8 ? launch_split<4, 2, 8>(g, F, I, O, accumulate, vec, stream)
+                                : launch_split<4, 2, 4>(g, F, I, O, accumulate, vec, stream);
+        if (c.mt == 64)
+            return c.share == 8 ? launch_split<4, 1, 8>(g, F, I, O, accumulate, vec, stream)
+                                : launch_split<4, 1, 4>(g, F, I, O, accumulate, vec, stream);
+        if (c.mt == 32)
+            return c.nt == 32 ? launch_split<2, 2, 8>(g, F, I, O, accumulate, vec, stream)
+                              : launch_split<2, 4, 8>(g, F, I, O, accumulate, vec, stream);
+        return launch_split<1, 1, 16>(g, F, I, O, accumulate, vec, stream);
+    case kRuns:
+        return c.share == 4 ? launch_runs<4, 2, 4>(g, F, I, O, accumulate, vec, stream)
+                            : launch_runs<4, 2, 2>(g, F, I, O, accumulate, vec, stream);
+    case kDirect:
+        if (c.mt == 64)
+            return c.nt == 64 ? launch_direct<2, 2>(g, F, I, O, accumulate, vec, c.share, stream)
+                              : launch_direct<2, 4>(g, F, I, O, accumulate, vec, 1, stream);
+        return c.nt == 64 ? launch_direct<4, 2>(g, F, I, O, accumulate, vec, 1, stream)
+                          : launch_direct<4, 4>(g, F, I, O, accumulate, vec, 1, stream);
+    default:
+        if (c.mt == 64 && c.nt == 64) return launch<64, 64>(g, F, I, O, accumulate, vec, cus, stream);
+        if (c.mt == 64 && c.nt == 128) return launch<64, 128>(g, F, I, O, accumulate, vec, cus, stream);
+        if (c.mt == 64) return launch<64, 256>(g, F, I, O, accumulate, vec, cus, stream);
+        if (c.mt == 128) return launch<128, 128>(g, F, I, O, accumulate, vec, cus, stream);
+        return launch<192, 128>(g, F, I, O, accumulate, vec, cus, stream);
     }
-    if (c22 == best) return launch_split<2, 2, 8>(g, F, I, O, accumulate, vec, stream);
-    if (c24 == best) return launch_split<2, 4, 8>(g, F, I, O, accumulate, vec, stream);
-    return launch_split<1, 1, 16>(g, F, I, O, accumulate, vec, stream);
 }
 
 int device_cus()
@@ -1000,11 +1162,13 @@ extern "C" int convgemm_out_size(int h, int k, int stride, int pad)
     return convgemm::out_size(h, k, stride, pad);
 }
 
-extern "C" int convgemm_f32(int kn, int kh, int kw, int ci, int hi, int wi, int b, int stride, int pad,
-                            const float* F, const float* I, float* O, int accumulate, int path, int mt, int nt,
-                            hipStream_t stream)
+namespace convgemm {
+namespace {
+
+// The layer's geometry, or -i when argument i is out of range (b = 0 leaves g
+// without output positions).
+int make_geometry(int kn, int kh, int kw, int ci, int hi, int wi, int b, int stride, int pad, Geometry& g)
 {
-    using namespace convgemm;
     if (kn < 1) return -1;
     if (kh < 1) return -2;
     if (kw < 1) return -3;
@@ -1023,23 +1187,6 @@ extern "C" int convgemm_f32(int kn, int kh, int kw, int ci, int hi, int wi, int 
     if ((int64_t)ho * wo * b >= ((int64_t)1 << 31)) return -7;
     if ((int64_t)hi * wi * ci * b >= ((int64_t)1 << 30)) return -7;
     if (kn >= (1 << 24) || (int64_t)kn * kh * kw * ci >= ((int64_t)1 << 30)) return -1;
-    if (accumulate != 0 && accumulate != 1) return -13;
-    // path: 0 automatic, 1 LDS-staged gather, 2 register-direct (no padding,
-    // contraction up to kDirectMaxK rows: its row table lives in LDS)
-    const int64_t kk = (int64_t)kh * kw * ci;
-    if (path < 0 || path > 2 || (path == 2 && (pad != 0 || kk > kDirectMaxK)) || (path == 0 && (mt || nt)))
-        return -14;
-    const bool lds_tile = (mt == 64 && (nt == 64 || nt == 128 || nt == 256)) || (mt == 128 && nt == 128) ||
-                          (mt == 192 && nt == 128);
-    const bool direct_tile = (mt == 64 || mt == 128) && (nt == 64 || nt == 128);
-    if (path == 1 && !(lds_tile || (mt == 0 && nt == 0))) return -15;
-    if (path == 2 && !(direct_tile || (mt == 0 && nt == 0))) return -15;
-    if (b == 0) return CONVGEMM_OK;
-    if (!F) return -10;
-    if (!I) return -11;
-    if (!O) return -12;
-
-    Geometry g;
     g.M = kn;
     g.K = kh * kw * ci;
     g.ci = ci;
@@ -1057,90 +1204,56 @@ extern "C" int convgemm_f32(int kn, int kh, int kw, int ci, int hi, int wi, int 
     g.sample = (int64_t)hi * wi * ci;
     g.ibytes = (uint32_t)(g.sample * b * 4);
     g.fbytes = (uint32_t)((int64_t)kn * g.K * 4);
+    return CONVGEMM_OK;
+}
+
+}  // namespace
+}  // namespace convgemm
+
+extern "C" int convgemm_choice(int kn, int kh, int kw, int ci, int hi, int wi, int b, int stride, int pad, int* out)
+{
+    using namespace convgemm;
+    Geometry g;
+    const int r = make_geometry(kn, kh, kw, ci, hi, wi, b, stride, pad, g);
+    if (r != CONVGEMM_OK) return r;
+    if (!out) return -10;
+    const Choice c = b == 0 ? Choice{0, 0, 0, 0} : choose(g, device_cus());
+    out[0] = c.family;
+    out[1] = c.mt;
+    out[2] = c.nt;
+    out[3] = c.share;
+    return CONVGEMM_OK;
+}
+
+extern "C" int convgemm_f32(int kn, int kh, int kw, int ci, int hi, int wi, int b, int stride, int pad,
+                            const float* F, const float* I, float* O, int accumulate, int path, int mt, int nt,
+                            hipStream_t stream)
+{
+    using namespace convgemm;
+    Geometry g;
+    const int r = make_geometry(kn, kh, kw, ci, hi, wi, b, stride, pad, g);
+    if (r != CONVGEMM_OK) return r;
+    if (accumulate != 0 && accumulate != 1) return -13;
+    // path: 0 automatic, 1 LDS-staged gather, 2 register-direct (no padding,
+    // contraction up to kDirectMaxK rows: its row table lives in LDS)
+    if (path < 0 || path > 2 || (path == 2 && (pad != 0 || g.K > kDirectMaxK)) || (path == 0 && (mt || nt)))
+        return -14;
+    const bool lds_tile = (mt == 64 && (nt == 64 || nt == 128 || nt == 256)) || (mt == 128 && nt == 128) ||
+                          (mt == 192 && nt == 128);
+    const bool direct_tile = (mt == 64 || mt == 128) && (nt == 64 || nt == 128);
+    if (path == 1 && !(lds_tile || (mt == 0 && nt == 0))) return -15;
+    if (path == 2 && !(direct_tile || (mt == 0 && nt == 0))) return -15;
+    if (b == 0) return CONVGEMM_OK;
+    if (!F) return -10;
+    if (!I) return -11;
+    if (!O) return -12;
 
     const int vec = (kn % 4 == 0) && ((uintptr_t)O % 16 == 0);
     const int cus = device_cus();
-    hipError_t e;
-    // automatic, enough channels that blocks of 16 waste no more than a third of
-    // the products (three channels would run at a fifth): the channel-block
-    // kernels; with a partial block and a large unpadded grid at unit stride the
-    // register-direct kernel, which wastes none, is faster (256 x 102660 x 297,
-    // 33 channels: 144 against 217 us)
-    const bool direct = pad == 0 && stride == 1 && kk <= kDirectMaxK;
-    const bool large = (int64_t)((g.M + 63) / 64) * ((g.N + 127) / 128) >= 4 * (int64_t)cus;
-    if (path == 0 && (ci + 15) / 16 * 16 * 2 <= 3 * ci && !(ci % 16 != 0 && direct && large) &&
-        g.ibytes <= kOutside && g.fbytes <= kOutside) {
-        e = launch_channel_blocks(g, F, I, O, accumulate, vec, cus, stream);
-        return e == hipSuccess ? CONVGEMM_OK : CONVGEMM_ERR_HIP_BASE - (int)e;
-    }
-    // few channels, strided and not padded, a tap height that runs of four cover
-    // with at most a third of waste, filters in wide loads, and a contraction of
-    // at least 64 taps whose table fits LDS: the runs kernel.  Old path against it:
-    // kh = 5 (two runs for five taps, 64 x 14400 x 250) 13 against 17 us, an odd
-    // filter count (33 x 61504 x 75) 16 against 21, 48 taps (384 x 63504) 39
-    // against 39; stride 1 (7 x 7, 64 x 131072 x 147) 31 against 35, where the
-    // register-direct kernel reads contiguous runs already.  Four waves share the
-    // contraction from 16 groups on (64 x 46656 x 363: 33 us before, 31 with two
-    // waves, 26 with four), two below (64 x 190096 x 147: 52, 46, 49).
-    const size_t nruns = run_count(g);
-    if (path == 0 && pad == 0 && stride > 1 && kn % 4 == 0 && kh >= 4 && kh != 5 && nruns >= 16 && nruns <= 2048 &&
-        g.ibytes <= kOutside && g.fbytes <= kOutside) {
-        e = nruns > 60 ? launch_runs<4, 2, 4>(g, F, I, O, accumulate, vec, stream)
-                       : launch_runs<4, 2, 2>(g, F, I, O, accumulate, vec, stream);
-        return e == hipSuccess ? CONVGEMM_OK : CONVGEMM_ERR_HIP_BASE - (int)e;
-    }
-    // otherwise the register-direct kernel for unit-stride convolutions
-    // without padding (the im2col columns of neighbouring
-    // positions are then contiguous input runs that the caches serve well);
-    // the LDS-staged gather otherwise (measured: the direct kernel is slower
-    // at stride 4, where each load instruction spans four times the lines)
-    if (path == 0) path = direct ? 2 : 1;
-    if (path == 2) {
-        int dm = mt, dn = nt;
-        if (dm == 0) {
-            // measured on the AlexNet layers: 64 x 128 while that still gives
-            // four tiles per CU; 128 x 64 for filter counts divisible by 128
-            // with at least 1.5 tiles per CU; 64 x 64 otherwise
-            const int64_t t64x128 = (int64_t)((g.M + 63) / 64) * ((g.N + 127) / 128);
-            const int64_t t128x64 = (int64_t)((g.M + 127) / 128) * ((g.N + 63) / 64);
-            if (t64x128 >= 4 * (int64_t)cus)
-                dm = 64, dn = 128;
-            else if (g.M % 128 == 0 && 2 * t128x64 >= 3 * (int64_t)cus)
-                dm = 128, dn = 64;
-            else
-                dm = 64, dn = 64;
-        }
-        // grids short even with the smallest tile, and long contractions: the
-        // contraction of each tile is split over several workgroups (atomic
-        // adds into O) so that every CU holds about three, each part keeping
-        // at least 64 groups of 16 (measured on AlexNet layer 8, 608 tiles:
-        // 0.227 -> 0.209 ms; layer 7's 456 larger tiles were slower split)
-        int kparts = 1;
-        if (mt == 0 && dm == 64 && dn == 64) {
-            const int64_t tl = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
-            const int ngroups = (g.K + 15) / 16;
-            while (kparts < 4 && tl * kparts < 3 * (int64_t)cus && ngroups / (2 * kparts) >= 64) kparts *= 2;
-        }
-        if (dm == 64 && dn == 64)
-            e = launch_direct<2, 2>(g, F, I, O, accumulate, vec, kparts, stream);
-        else if (dm == 64)
-            e = launch_direct<2, 4>(g, F, I, O, accumulate, vec, 1, stream);
-        else if (dn == 64)
-            e = launch_direct<4, 2>(g, F, I, O, accumulate, vec, 1, stream);
-        else
-            e = launch_direct<4, 4>(g, F, I, O, accumulate, vec, 1, stream);
-        return e == hipSuccess ? CONVGEMM_OK : CONVGEMM_ERR_HIP_BASE - (int)e;
-    }
-    Tile t = (mt == 0 && nt == 0) ? choose_tile(g.M, g.N, cus) : Tile{mt, nt};
-    if (t.mt == 64 && t.nt == 64)
-        e = launch<64, 64>(g, F, I, O, accumulate, vec, cus, stream);
-    else if (t.mt == 64 && t.nt == 128)
-        e = launch<64, 128>(g, F, I, O, accumulate, vec, cus, stream);
-    else if (t.mt == 64)
-        e = launch<64, 256>(g, F, I, O, accumulate, vec, cus, stream);
-    else if (t.mt == 128)
-        e = launch<128, 128>(g, F, I, O, accumulate, vec, cus, stream);
-    else
-        e = launch<192, 128>(g, F, I, O, accumulate, vec, cus, stream);
+    const Choice c = path == 0   ? choose(g, cus)
+                     : mt != 0   ? Choice{path == 1 ? kStaged : kDirect, mt, nt, 1}
+                     : path == 1 ? staged_choice(g, cus)
+                                 : direct_choice(g, cus);
+    const hipError_t e = launch_choice(g, c, F, I, O, accumulate, vec, cus, stream);
     return e == hipSuccess ? CONVGEMM_OK : CONVGEMM_ERR_HIP_BASE - (int)e;
 }
