@@ -1104,8 +1104,14 @@ Choice choose(const Geometry& g, int cus)
     // against 39; stride 1 (7 x 7, 64 x 131072 x 147) 31 against 35, where the
     // register-direct kernel reads contiguous runs already.  Four waves share the
     // contraction from 16 groups on (64 x 46656 x 363: 33 us before, 31 with two
-    // waves, 26 with four), two below (64 x 190096 x 147: 52, 46, 49).
+    // waves, 26 with four), two below (64 x 190096 x 147: 52, 46, 49).  The general
+    // kernel's 128 x 128 tiles are faster where the runs waste more than a seventh
+    // (384 x 130200 x 243, kh = 9: 258 against 316; 640 x 91250 x 288, kh = 6: 371,
+    // 446), and slower with less waste (medians of 20 layers each: kh = 6, 9, 10 the
+    // runs take 1.08, 1.09, 1.01 of their time, kh = 7, 11, 8 0.92, 0.94, 0.88).
     const size_t nruns = run_count(g);
+    const bool wasteful = 7 * ((g.kh + 3) / 4 * 4) > 8 * g.kh;
+    if (general.mt == 128 && wasteful) return general;
     if (g.p == 0 && g.s > 1 && g.M % 4 == 0 && g.kh >= 4 && g.kh != 5 && nruns >= 16 && nruns <= 2048)
         return Choice{kRuns, 64, 32, nruns > 60 ? 4 : 2};
     return general;

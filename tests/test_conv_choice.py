@@ -56,6 +56,22 @@ def test_layers_that_gain_from_channel_blocks_keep_them(case):
     assert choice(case)[0] == BLOCKS
 
 
+# kn, k, ci, hi, wi, b, stride; the LDS-staged 128 x 128 tile against runs of taps
+@pytest.mark.parametrize("case,family", [
+    ((384, 9, 3, 158, 192, 42, 3), STAGED),      # 258 against 316
+    ((640, 6, 8, 223, 155, 25, 3), STAGED),      # 371, 446
+    ((256, 10, 8, 114, 150, 26, 2), STAGED),     # 381, 423
+    ((384, 8, 3, 158, 192, 42, 3), RUNS),
+    ((640, 7, 8, 223, 155, 25, 3), RUNS),
+    ((256, 11, 8, 114, 150, 26, 2), RUNS),
+    ((96, 9, 3, 158, 192, 42, 3), RUNS),         # no 128 x 128 tile
+    ((384, 9, 3, 58, 92, 4, 3), RUNS),           # too few of them
+])
+def test_wasteful_runs_go_to_the_wide_staged_tile(case, family):
+    kn, k, ci, hi, wi, b, s = case
+    assert lt.conv_choice(kn, k, k, ci, hi, wi, b, s, 0)[0] == family
+
+
 def test_every_choice_can_be_launched():
     legal = {(STAGED, 64, 64, 1), (STAGED, 128, 128, 1),
              (DIRECT, 64, 64, 1), (DIRECT, 64, 64, 2), (DIRECT, 64, 64, 4), (DIRECT, 64, 128, 1), (DIRECT, 128, 64, 1),
