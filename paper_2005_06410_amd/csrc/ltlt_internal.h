@@ -63,12 +63,12 @@ struct UpdateArgs {
 // at a cost of about 20 us per launch.
 bool cooperative_panels();
 template <typename K, typename A>
-hipError_t launch_resident_grid(K kernel, unsigned grid, unsigned block, size_t lds, hipStream_t s, const A& arg) {
+hipError_t launch_resident_grid(K kernel, dim3 grid, unsigned block, size_t lds, hipStream_t s, const A& arg) {
   A copy = arg;
   void* args[] = {&copy};
   if (cooperative_panels())
-    return hipLaunchCooperativeKernel((const void*)kernel, dim3(grid), dim3(block), args, (unsigned)lds, s);
-  return hipLaunchKernel((const void*)kernel, dim3(grid), dim3(block), args, lds, s);
+    return hipLaunchCooperativeKernel((const void*)kernel, grid, dim3(block), args, (unsigned)lds, s);
+  return hipLaunchKernel((const void*)kernel, grid, dim3(block), args, lds, s);
 }
 
 template <typename T> hipError_t launch_panel(const PanelArgs& a, size_t lds, hipStream_t s);
@@ -128,7 +128,8 @@ template <typename T> hipError_t launch_cpfaffian(int n, const void* A, int64_t 
                                                   double* logabs, double* phase, const int* status, hipStream_t s);
 
 // Solve with the factors.
-constexpr int kSolveRhs = 4;                    // right-hand sides per pass
+constexpr int kSolveGroup = 4;                  // right-hand sides of one workgroup (one per wave)
+constexpr int kSolveRhs = 8;                    // right-hand sides per pass: up to two groups side by side
 struct SolveWork {
   int* perm;          // [n]
   int* cnt;           // [2n] counters (steps per target position, fill)
@@ -139,7 +140,7 @@ struct SolveWork {
   void* Y;            // [ldy][kSolveRhs]
   void* W;            // [ldy][kSolveRhs]
   int64_t ldy;
-  uint64_t* box;      // [blocks][kSolveRhs][64][2] stamped solution words
+  uint64_t* box;      // [kSolveRhs / kSolveGroup][blocks][kSolveGroup][64][2] stamped solution words
   int* status;
   void* dinv;         // [3][blocks][64 * 64]: inverses of the diagonal blocks of L and the
                       // matrices of the nearest dependency of each substitution

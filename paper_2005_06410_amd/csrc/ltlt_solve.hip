@@ -35,7 +35,7 @@
 //    then re-runs its chunk from its starting value with the recurrence as
 //    written; one workgroup per (right-hand side, chain), the reciprocals of
 //    alpha formed in parallel beforehand.
-// Right-hand sides are taken kSolveRhs at a time.
+// Right-hand sides are taken kSolveRhs at a time, kSolveGroup to a workgroup.
 
 #include "ltlt_device.h"
 #include "ltlt_exchange.h"
@@ -237,8 +237,8 @@ struct SolveTriArgs {
   int nblk;
   void* Y;
   int64_t ldy;
-  int nr;             // right-hand sides of this pass (<= kSolveRhs)
-  uint64_t* box;      // [nblk][kSolveRhs][kSB][2] stamped solution words
+  int nr;             // right-hand sides of this pass (<= kSolveRhs); a workgroup sees its group's
+  uint64_t* box;      // [group][nblk][kSolveGroup][kSB][2] stamped solution words
   unsigned stamp;     // stamp of this launch (never 0)
   int* status;
   const void* Dinv;   // inverses of the diagonal blocks of L: [nblk][64 * 64], column-major
@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(kSThreads) solve_mmat_kernel(const T* A, int64
 // with unspecified values, so that no wave leaves its workgroup's barriers.
 template <typename T, int NQ>
 __device__ __forceinline__ void wait_words(const SolveTriArgs& a, int sb, int at, int naps, T (&v)[NQ]) {
-  const uint64_t* w = a.box + ((size_t)sb * kSolveRhs * kSB + at) * 2;
+  const uint64_t* w = a.box + ((size_t)sb * kSolveGroup * kSB + at) * 2;
   const uint64_t t0 = wall_ticks();
   for (;;) {
     const int st = ld_coh(a.status);
@@ -493,8 +493,14 @@ __device__ __forceinline__ T lane_sums(const T (&v)[16], int lane) {
 // backward with a workgroup barrier or two per tile, the solution through
 // LDS, eight right-hand-side slots always multiplied and the backward tiles
 // read across columns; 0.35 and 0.41 now.
+// Groups of four right-hand sides (blockIdx.y) are chains of their own, so they
+// run side by side: MEASURED
 template <typename T, bool UPPER, int NQ>
 __global__ void __launch_bounds__(kSThreads, 1) solve_tri_kernel(SolveTriArgs a) {
+  static_assert(NQ <= kSThreads / kWave && kSolveGroup <= kSThreads / kWave, "a wave solves one right-hand side");
+  a.nr = min(a.nr - (int)blockIdx.y * kSolveGroup, NQ);
+  a.Y = static_cast<T*>(a.Y) + (int64_t)blockIdx.y * kSolveGroup * a.ldy;
+  a.box += (size_t)blockIdx.y * a.nblk * kSolveGroup * kSB * 2;
   extern __shared__ __align__(16) unsigned char smem[];
   T* dt = reinterpret_cast<T*>(smem);              // D_b^{-1} (forward) or D_b^{-T}, as load_mat reads it
   T* mt = dt + kSB * kSB;                          // Mf_b or Mb_b, likewise
@@ -610,7 +616,7 @@ __global__ void __launch_bounds__(kSThreads, 1) solve_tri_kernel(SolveTriArgs a)
         x -= mat_vec(m, near[0], lane);
       }
       if (d0 + lane < n) Y[(int64_t)(d0 + lane) + (int64_t)g * ldy] = x;
-      box_put(&a.box[(((size_t)b * kSolveRhs + g) * kSB + lane) * 2], d0 + lane < n ? x : T(0), a.stamp);
+      box_put(&a.box[(((size_t)b * kSolveGroup + g) * kSB + lane) * 2], d0 + lane < n ? x : T(0), a.stamp);
     }
     lds_barrier();                                 // dt, mt and part are reused by the next block
   }
@@ -632,16 +638,17 @@ hipError_t launch_solve_tri_q(const SolveTriArgs& a, hipStream_t s) {
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
   if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kSThreads, lds)) != hipSuccess) return e;
-  const int cap = per_cu * cus;
+  const int groups = (a.nr + NQ - 1) / NQ;         // NQ == kSolveGroup when there are two
+  const int cap = per_cu * cus / groups;
   if (cap <= 0) return hipErrorInvalidValue;
-  return launch_resident_grid(solve_tri_kernel<T, UPPER, NQ>, (unsigned)(a.nblk < cap ? a.nblk : cap), kSThreads, lds,
-                              s, a);
+  return launch_resident_grid(solve_tri_kernel<T, UPPER, NQ>, dim3((unsigned)(a.nblk < cap ? a.nblk : cap), groups),
+                              kSThreads, lds, s, a);
 }
 template <typename T, bool UPPER>
 hipError_t launch_solve_tri(const SolveTriArgs& a, hipStream_t s) {
   if (a.nr == 1) return launch_solve_tri_q<T, UPPER, 1>(a, s);
   if (a.nr == 2) return launch_solve_tri_q<T, UPPER, 2>(a, s);
-  return launch_solve_tri_q<T, UPPER, kSolveRhs>(a, s);
+  return launch_solve_tri_q<T, UPPER, kSolveGroup>(a, s);
 }
 
 // Stamps of the mailbox words: a process-wide counter that skips 0 (zeroed
@@ -677,7 +684,7 @@ hipError_t launch_solve(int n, const T* A, int64_t lda, const int* ipiv, int nrh
     // The solution words validate by the stamp of their launch, and stamps are
     // small integers: clear the words first, so that whatever an earlier call
     // left in this part of the workspace can never carry a current stamp.
-    const int words = nblk * kSolveRhs * kSB * 2 * 2;   // as 32-bit halves
+    const int words = nblk * (nrhs > kSolveGroup ? kSolveRhs : kSolveGroup) * kSB * 2 * 2;   // as 32-bit halves
     hipLaunchKernelGGL(zero_ints_kernel, dim3((words + 255) / 256), dim3(256), 0, s, reinterpret_cast<int*>(w.box),
                        words);
     if ((e = hipGetLastError()) != hipSuccess) return e;
