@@ -198,7 +198,8 @@ __device__ __forceinline__ TileRange tiles_of_block(int b, int nblocks, int ntil
   return TileRange{lo + l, hi, cx};
 }
 
-template <typename T, bool DMA>
+// INNER: the epilogue's running addresses (see there).
+template <typename T, bool DMA, bool INNER>
 __global__ void __launch_bounds__(kThreads, kUpdateWgPerCu) update_kernel(UpdateArgs a) {
   typedef typename Mfma<T>::acc_t acc_t;
   // operand chunks As[2][kKC*kLd], Bs[2][kKC*kLd]; reused by the epilogue
@@ -316,14 +317,14 @@ __global__ void __launch_bounds__(kThreads, kUpdateWgPerCu) update_kernel(Update
   // turned.  One running address and one sign per lane then serve all columns but
   // the displaced ones (mcols; 1 % at m = 16256), which are looked up one by one.
   // The general gather forms a 64-bit address, a mask and a sign for every entry,
-  // vector work that the other waves' MFMAs wait for.  Measured, general against
-  // this (us, bit-identical): fp64 K = 129 m = 16256 776, 750, m = 8000
-  // 209, 200, m = 2300 35, 35; fp32 K = 128 m = 16256 449, 393, m = 4000 45, 42.
-  // The register-staged fp64 kernel keeps the general form: it spills more with
-  // both (m = 2003 44 against 52 us).
+  // vector work that the other waves' MFMAs wait for; so this form pays where
+  // there are such waves and MFMAs, and in fp64 costs up to 11 % where there are
+  // not (see launch_update).  Measured, general against this (us, bit-identical):
+  // fp64 K = 129 m = 16256 759, 730, m = 8000 199, 193; fp32 K = 129 m = 12000 262,
+  // 239, m = 3000 34.3, 33.7.  The register-staged fp64 kernel keeps the general
+  // form: it spills more with both (m = 2003 44 against 52 us).
   const int cw = c0 + wc * 64;                     // the wave's columns
-  constexpr bool kInner = DMA || sizeof(T) == 4;
-  const bool inner = kInner && r0 >= c0 + kMT && r0 + kMT <= m && __ballot(pr >= c0 && pr < r0) == 0;
+  const bool inner = INNER && r0 >= c0 + kMT && r0 + kMT <= m && __ballot(pr >= c0 && pr < r0) == 0;
   const unsigned long long mcols = __ballot(pcol[wc * 64 + lane] != cw + lane);
   const bool low = pr >= r0;
   const T sgn = low ? T(1) : T(-1);
@@ -495,12 +496,23 @@ hipError_t launch_update(const UpdateArgs& a, hipStream_t s) {
              (reinterpret_cast<uintptr_t>(a.Bt) % 16 == 0) && (a.ldl % 2 == 0) && (a.ldb % 2 == 0) &&
              ((a.m % 2 == 0) || a.pad_row);
   if constexpr (std::is_same<T, double>::value) {
+    // Running addresses in the epilogue where other tiles' products run beside it:
+    // more than one round of tiles and more than 32 columns.  Elsewhere they are
+    // mostly the slower form (general, running addresses, us): m = 2300 K = 65 23.7,
+    // 24.6; m = 4300 K = 65 46.9, 49.2, K = 1 29.2, 32.5; m = 6500 K = 8 61.2, 65.6,
+    // K = 32 74.0, 75.1, but K = 33 76.5, 76.0, K = 65 98.0, 94.3; m = 4870 K = 33
+    // 58.1, 52.4.
+    if (dma && nblk > kUpdateGrid && a.K > 32) {
+      hipLaunchKernelGGL((update_kernel<T, true, true>), dim3((unsigned)grid), dim3(kThreads), 0, s, c);
+      return hipGetLastError();
+    }
     if (dma) {
-      hipLaunchKernelGGL((update_kernel<T, true>), dim3((unsigned)grid), dim3(kThreads), 0, s, c);
+      hipLaunchKernelGGL((update_kernel<T, true, false>), dim3((unsigned)grid), dim3(kThreads), 0, s, c);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((update_kernel<T, false>), dim3((unsigned)grid), dim3(kThreads), 0, s, c);
+  // fp32: running addresses always (0.89 to 1.01 of the general form's time)
+  hipLaunchKernelGGL((update_kernel<T, false, sizeof(T) == 4>), dim3((unsigned)grid), dim3(kThreads), 0, s, c);
   return hipGetLastError();
 }
 

@@ -17,7 +17,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("m,K,odd", [(2, 1, 0), (63, 4, 1), (64, 5, 0), (65, 31, 0), (129, 33, 1), (200, 129, 0),
-                                     (700, 130, 1), (1984, 36, 0), (1985, 36, 0), (1985, 37, 1), (2111, 129, 0), (2304, 20, 0)])
+                                     (700, 130, 1), (1984, 36, 0), (1985, 36, 0), (1985, 37, 1), (2111, 129, 0), (2304, 20, 0),
+                                     # one round of 128 x 128 tiles and two; either side of 32 columns
+                                     (4864, 33, 0), (4866, 32, 0), (4866, 33, 0), (5000, 129, 0)])
 def test_update_sizes(m, K, odd, dtype):
     import paper_2005_06410_amd as lt
     g = torch.Generator(device="cuda")
