@@ -1078,12 +1078,12 @@ Choice choose(const Geometry& g, int cus)
     // enough channels that blocks of 16 waste no more than a third of the
     // products (three channels would run at a fifth): the channel-block kernels.
     // With whole blocks, wide filter loads and more than 16 groups they are the
-    // faster ones (2379 measured layers: 0.30 of the general kernel's time in the
+    // faster ones (2379 measured layers: 0.32 of the general kernel's time in the
     // mean, none slower by more than 12 %).  Elsewhere the estimates decide: a
     // contraction of a few groups leaves the waves that share a tile without work
     // (16 x 125440 x 16: 35 against 7.5 us general), partial blocks and filters
     // loaded one by one cost too much on many tiles (33 x 125440 x 64: 35 against
-    // 20), and so do wide strides (870 x 2700 x 3456, stride 4: 378 against 249).
+    // 20), and so do wide strides (298 x 4290 x 160, stride 4: 19.2 against 14.3).
     // Over 13130 measured layers the blocks alone took 0.515 of the general
     // kernels' time in the mean but were slower by more than 4 % on 1207 of them;
     // with this rule 0.501, and on 127.  With a partial block and a large unpadded

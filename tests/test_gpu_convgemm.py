@@ -12,8 +12,8 @@ convolution oracle (direct loops of the paper's Figure 4, fp64).
   with many (16-row chunks), with and without padding; strides 1-4, padding
   0-3, non-square inputs and filters, 1x1 filters, a single output position, an empty batch, kn not a
   multiple of 4 and a misaligned output (scalar epilogue), accumulate mode;
-* short grids with long contractions, whose tiles' contractions the
-  automatic choice splits over several workgroups (atomic adds), exact and
+* short grids with long contractions, whose tiles' contractions the register-
+  direct kernel splits over several workgroups (atomic adds), exact and
   accumulating;
 * the AlexNet layers of the paper's Table 2 at b = 2 in full, and at the
   benchmarked b = 80 on sampled outputs (each computed one by one by the
@@ -206,44 +206,75 @@ def test_short_contractions_integer_exact(path, kn, kh, kw, ci):
     assert np.array_equal(got.astype(np.float64), oc.conv_direct(F, I, 1, 0))
 
 
-# Short grid, long contraction: the automatic register-direct choice (64 x 64
-# tiles, fewer than three per CU) splits each tile's contraction over two or
-# four workgroups that add into O atomically (O cleared first unless
+# Short grid, long contraction: the register-direct kernel with its tile left open
+# (64 x 64, fewer than three tiles per CU) splits each tile's contraction over two
+# or four workgroups that add into O atomically (O cleared first unless
 # accumulating).  K = 3*3*300 = 2700 (169 groups of 16: two parts), and
-# 3*3*600 = 5400 (338 groups: four parts); kn = 70 is not a multiple of 4.
-SPLITS = [(70, 3, 3, 300, 9, 8, 2), (36, 3, 3, 600, 7, 9, 3)]
+# 3*3*600 = 5400 (338 groups: four parts); kn = 70 is not a multiple of 4.  By
+# itself the library takes this path for few channels and large taps: K = 15*15*10
+# = 2250 (two parts) and 23*23*8 = 4232 (four).
+# (case, path, parts)
+SPLITS = [((70, 3, 3, 300, 9, 8, 2), 2, 2), ((36, 3, 3, 600, 7, 9, 3), 2, 4),
+          ((70, 15, 15, 10, 20, 21, 2), 0, 2), ((36, 23, 23, 8, 26, 29, 3), 0, 4)]
 
 
-@pytest.mark.parametrize("g", SPLITS)
-def test_split_contraction_integer_exact(g):
+def split_parts(g, path):
+    """Parts of the contraction: what the library says it chooses, or (path 2) the
+    rule's fewest parts of at least 64 groups that reach three workgroups per CU
+    (these grids never do)."""
+    kn, kh, kw, ci, hi, wi, b = g
+    if path == 0:
+        family, mt, nt, parts = lt.conv_choice(kn, kh, kw, ci, hi, wi, b)
+        assert (family, mt, nt) == (2, 64, 64)
+        return parts
+    groups, parts = (kh * kw * ci + 15) // 16, 1
+    while parts < 4 and groups // (2 * parts) >= 64:
+        parts *= 2
+    return parts
+
+
+@pytest.mark.parametrize("g,path,parts", SPLITS)
+def test_split_contraction_integer_exact(g, path, parts):
     kn, kh, kw, ci, hi, wi, b = g
     F, I = int_case(kn, kh, kw, ci, hi, wi, b, 57, -2, 2)
     ho, wo = hi - kh + 1, wi - kw + 1
-    print(f"[conv] split contraction K={kh * kw * ci} kn={kn} N={ho * wo * b}", flush=True)
+    print(f"[conv] split contraction K={kh * kw * ci} kn={kn} N={ho * wo * b} path {path}", flush=True)
+    assert split_parts(g, path) == parts
     # a stale output must not leak into the result
     out = dev(np.asfortranarray(np.full((kn, ho, wo, b), 9.0, dtype=np.float32)))
-    got = host(run(F, I, 1, 0, out=out))
+    got = host(run(F, I, 1, 0, out=out, path=path))
     assert np.array_equal(got.astype(np.float64), oc.conv_direct(F, I, 1, 0))
     # accumulate: O += conv(F, I), exact for integers
     O0 = sc.int_tensor((kn, ho, wo, b), 58, -5, 5, index=7)
-    got = host(run(F, I, 1, 0, out=dev(O0), accumulate=True))
+    got = host(run(F, I, 1, 0, out=dev(O0), accumulate=True, path=path))
     assert np.array_equal(got.astype(np.float64), oc.conv_direct(F, I, 1, 0) + O0.astype(np.float64))
 
 
-@pytest.mark.parametrize("g", SPLITS)
-def test_split_contraction_gaussian(g):
+@pytest.mark.parametrize("g,path,parts", SPLITS)
+def test_split_contraction_gaussian(g, path, parts):
     kn, kh, kw, ci, hi, wi, b = g
     F, I = gauss_case(kn, kh, kw, ci, hi, wi, b, 59)
-    got = host(run(F, I, 1, 0))
+    got = host(run(F, I, 1, 0, path=path))
     check_close(got, oc.conv_direct(F, I, 1, 0), bound(F, I, 1, 0, oc), f"split {g}")
 
 
 def test_long_contraction_falls_back_to_lds_staging():
-    """K = 3*3*2000 = 18000 rows exceeds the register-direct kernel's row table:
-    the automatic choice takes the LDS-staged kernel."""
+    """K = 43*43*9 = 16641 rows exceeds the register-direct kernel's row table: the
+    automatic choice for few channels takes the LDS-staged kernel."""
+    kn, kh, kw, ci, hi, wi, b = 8, 43, 43, 9, 45, 46, 2
+    F, I = int_case(kn, kh, kw, ci, hi, wi, b, 56, -2, 2)
+    print("[conv] long contraction K=16641", flush=True)
+    assert lt.conv_choice(kn, kh, kw, ci, hi, wi, b)[0] == 1
+    got = host(run(F, I, 1, 0))
+    assert np.array_equal(got.astype(np.float64), oc.conv_direct(F, I, 1, 0))
+
+
+def test_long_contraction_of_many_channels():
+    """K = 3*3*2000 = 18000 rows: the channel-block kernels need no row table."""
     kn, kh, kw, ci, hi, wi, b = 8, 3, 3, 2000, 5, 6, 2
     F, I = int_case(kn, kh, kw, ci, hi, wi, b, 56, -2, 2)
     print("[conv] long contraction K=18000", flush=True)
+    assert lt.conv_choice(kn, kh, kw, ci, hi, wi, b)[0] == 3
     got = host(run(F, I, 1, 0))
     assert np.array_equal(got.astype(np.float64), oc.conv_direct(F, I, 1, 0))
 
