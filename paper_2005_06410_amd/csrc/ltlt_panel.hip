@@ -153,6 +153,7 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
   T l1 = T(0), l2 = T(0), alph1 = T(0);            // multipliers of steps t-1, t-2; alpha_{j+t-1}
   const int posc = min(pos, n - 1);                // in range for lanes without a row too
   int64_t rowat = (int64_t)posc * lda;             // element (., posc)
+  const int64_t at0 = (int64_t)(j + 1) + (int64_t)j * lda;
   // where this lane writes of its own row (gso: slots 4b .. 4b+3 of its part in
   // G; tso: the tail entry, part 0)
   constexpr unsigned TSZ = 2 * sizeof(T);
@@ -220,11 +221,15 @@ __global__ void __launch_bounds__(kPanelThreads, 1) panel_kernel(PanelArgs a) {
     if (p < 0) return;
 
     // ---- the next stored column S(pos, posw) = +A(pos, posw) below the
-    //      diagonal, -A(posw, pos) above; waited for in its refresh ----
+    //      diagonal, -A(posw, pos) above; waited for in its refresh.  The lanes
+    //      of the pivot row itself (and lanes without a row, standing in for the
+    //      last one) read the block's first entry: never the diagonal, which may
+    //      not be the caller's memory ----
     int64_t at1 = (int64_t)posw * lda + posc, at2 = rowat + posw;
     asm volatile("" : "+v"(at1), "+v"(at2));       // both formed, one selected: no branch
     below = pos > posw;
-    lvn = A[below ? at1 : at2];
+    const int64_t at = below ? at1 : at2;
+    lvn = A[posc == posw ? at0 : at];
     __builtin_amdgcn_sched_barrier(0);             // keep the loads ahead of the work below
 
     // ---- exchange positions k+1 and p (logical only); multiplier of step k;
