@@ -4,7 +4,12 @@
 // into the packing of the GEMM's B operand, so the augmented matrix of
 // section 3 is never formed in memory).
 //
-// Mapping to CDNA4.  One workgroup (4 waves, 2 x 2) owns an MT x NT tile of O^
+// Four kernels, chosen by choose() below: the LDS-staged gather described here
+// (any layer), a register-direct one (no padding), channel blocks (the usual
+// layers of eleven channels and more) and runs of taps (strided first layers),
+// each described where it stands.
+//
+// The LDS-staged gather.  One workgroup (4 waves, 2 x 2) owns an MT x NT tile of O^
 // (MT filters x NT output positions).  The contraction runs in chunks of
 // KC = 16 or 32 rows of im2col(I) (= columns of F^):
 //   * F^ chunk (MT x KC): coalesced loads along the filter index, kept in LDS
@@ -702,10 +707,13 @@ __global__ __launch_bounds__(64 * WAVES) void convgemm_split_kernel(Geometry g, 
 // first rows, which the run before it holds, are zeroed in both operands.  Lane
 // group q takes run 4 grp + q; a table of the runs' offsets is built in LDS when
 // the workgroup starts.  The waves of a workgroup split one 64 x 32 tile's runs,
-// as in the channel-block kernels.  What bounds it: three of a group's 16 taps
-// are zeros for kh = 11, and each lane's 16-byte loads still touch a line of
-// their own at stride 4.  Measured: AlexNet's first layer (64 x 93312 x 363,
-// stride 4) 59 -> 49 us, 16 x 16 patches (768 x 12544 x 768) 229 -> 129 us.
+// as in the channel-block kernels.  Measured: AlexNet's first layer (64 x 93312 x
+// 363, stride 4) 59 -> 49 us, 16 x 16 patches (768 x 12544 x 768) 229 -> 129 us.
+// What bounds it, on that first layer: the matrix instructions (46.6 us without
+// the loads, 23 with the loads alone; 31 at the matrix rate, one product in eleven
+// of them padding: 11 taps to 12, 99 runs to 100) and what does not overlap with
+// them, 10.8 us of launch, partial sums and stores; table and exchange cost under
+// 0.5 us each.
 struct Run {
     uint32_t f, i;     // byte offsets of its first row in F and of its first tap in I
     int skip;          // rows left out at its front: 0 to 3, or 4 past the last run
@@ -963,7 +971,9 @@ int64_t tile_count(const Geometry& g, int mt, int nt)
 // with at least 1.5 tiles per CU; 64 x 64 otherwise.  Grids short even with the
 // smallest tile, and long contractions: the contraction of each tile is split
 // over several workgroups (atomic adds into O) so that every CU holds about
-// three, each part keeping at least 64 groups of 16.
+// three, each part keeping at least 64 groups of 16 (608 tiles of 256 x 9680 x
+// 3456: 0.227 -> 0.209 ms; 456 larger tiles were slower so).  By itself the library
+// comes here with few channels and large taps.
 Choice direct_choice(const Geometry& g, int cus)
 {
     if (tile_count(g, 64, 128) >= 4 * (int64_t)cus) return Choice{kDirect, 64, 128, 1};
