@@ -84,8 +84,9 @@ int convgemm_f32(int kn, int kh, int kw, int ci, int hi, int wi, int b, int stri
                  const float* F, const float* I, float* O, int accumulate, int path, int mt, int nt,
                  hipStream_t stream);
 
-/* The kernel that path = 0 takes for a layer (host only; arguments and return
- * value as convgemm_f32, out = NULL is argument 10).  HOST int out[4]:
+/* The kernel that path = 0 takes for a layer on the current device (host only;
+ * without a device, on one of 256 CUs; arguments and return value as
+ * convgemm_f32, out = NULL is argument 10).  HOST int out[4]:
  *   out[0] = 1 LDS-staged gather, 2 register-direct, 3 channel blocks (16
  *            channels of one tap at a time), 4 runs of taps (four taps of a
  *            column at a time); 0 when b = 0;
